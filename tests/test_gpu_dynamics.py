@@ -129,6 +129,28 @@ def test_append_bit_exact(oracle, n, na, k):
     assert np.array_equal(ids_n.cpu().numpy(), oracle.append_rows(ids_o.cpu().numpy(), ids_a.cpu().numpy(), na))
 
 
+@pytest.mark.parametrize("n,na,k", [(4099, 1030, 5), (2050, 2050, 1), (1024, 0, 1024), (3, 1, 2), (2047, 1023, 3)])
+def test_append_across_quads_of_shifted_rows(n, na, k):
+    """Rows whose 16-byte quads straddle row ends and the seams between old,
+    added and frozen elements, into destinations off a 16-byte boundary."""
+    g = torch.Generator(device="cuda").manual_seed(n + na + k)
+    ctx = renderer_for(S.small_workload(1, 8, 1.0, 0, [(16, 16)], dist=3.0)).ctx
+
+    def mk(m, shift=0):
+        rows = [(3,), (3,), (4,), (), (12,)]
+        return DeviceParams(*[torch.randn(int(np.prod(r, dtype=int)) * m + shift, device="cuda", generator=g)[shift:]
+                              .view(*r, m) for r in rows], 1)
+    old, add, new = mk(n), mk(k, 1), mk(n + k, 3)
+    mo, vo, mn, vn = mk(na, 2), mk(na), mk(na + k, 1), mk(na + k)
+    ctx.append(old, add, new, na, moments=(mo, vo, mn, vn))
+    torch.cuda.synchronize()
+    for o, a, d in zip(old.tensors(), add.tensors(), new.tensors()):
+        assert torch.equal(d, torch.cat([o[..., :na], a, o[..., na:]], -1))
+    for src, dst in ((mo, mn), (vo, vn)):
+        for o, d in zip(src.tensors(), dst.tensors()):
+            assert torch.equal(d, torch.cat([o, torch.zeros_like(d[..., :k])], -1))
+
+
 def test_invalid_append_is_refused():
     rng = np.random.default_rng(1)
     Po = DeviceParams.from_scene(S.draw_scene(rng, 10, 1.0, 1))
