@@ -122,11 +122,8 @@ __host__ __device__ inline T* seg(void* ws, size_t off) {
 //        s = det(Q)/Q00 (= 1 / Sigma2_11); o = opacity
 //   r2 = (red, green, blue, 0)
 // ---------------------------------------------------------------------------
-// Evaluation of one splat at one pixel centre, in two parts so that a
-// wavefront can skip the second when no lane passes the first.  These are
-// the one place that decides whether a pixel takes a splat; the forward and
-// backward kernels call them on identical inputs, so they make identical
-// decisions bit for bit.
+// A splat at one pixel centre: offsets from its mean, e = dx + r dy, and the
+// base-2 power P.
 struct SplatGeom {
   float dx, dy, e, P;
 };
@@ -144,26 +141,11 @@ __device__ __forceinline__ float4 staged_conic(const float4& r1) {
   return make_float4(kMinusHalfLog2e * r1.x, r1.y, kMinusHalfLog2e * r1.z, r1.w);
 }
 
-// r1h: the record's second float4 after staged_conic; P is the base-2 power
-__device__ __forceinline__ SplatGeom splat_power(float pxc, float pyc, const float4& r0, const float4& r1h) {
+// Opacity of a splat at a pixel that passed the 3-sigma test (base-2 power
+// P2 >= kCutoff2), before the clamp at kAlphaMax.
+__device__ __forceinline__ float splat_opacity(float P2, float opacity) {
 #pragma clang fp contract(off)
-  SplatGeom g;
-  g.dx = (pxc - r0.x) - r0.z;
-  g.dy = (pyc - r0.y) - r0.w;
-  g.e = fmaf(r1h.y, g.dy, g.dx);
-  g.P = fmaf(r1h.x * g.e, g.e, r1h.z * (g.dy * g.dy));
-  return g;
-}
-
-// Opacity part, for a pixel that passed the 3-sigma test (base-2 power
-// P2 >= kCutoff2): returns whether alpha reaches the 1/255 skip threshold.
-__device__ __forceinline__ bool splat_alpha(float P2, float opacity, float& G, float& alpha, bool& clamped) {
-#pragma clang fp contract(off)
-  G = __builtin_amdgcn_exp2f(P2);
-  const float oG = opacity * G;
-  clamped = oG >= kAlphaMax;
-  alpha = clamped ? kAlphaMax : oG;
-  return alpha >= kAlphaMin;
+  return opacity * __builtin_amdgcn_exp2f(P2);
 }
 
 // ---- launchers implemented in the .hip files -------------------------------

@@ -158,6 +158,27 @@ def test_unbuilt_launch_shape_is_refused():
             renderer_for(w, **kw)
 
 
+@pytest.mark.parametrize("n", [1, 2, 65, 700])
+@pytest.mark.parametrize("tile,ppt,sw", [((8, 8), 1, 8), ((16, 16), 1, 16), ((16, 16), 4, 16), ((32, 32), 2, 32),
+                                         ((32, 32), 4, 16)])
+def test_backward_of_opaque_splats_matches_oracle(oracle, tile, ppt, sw, n):
+    """Splats on both sides of the opacity from which alpha can reach its clamp
+    (the adjoint's rare branch), in lists of odd and even lengths (visits of
+    two splats and of one left over), pixels stopping inside a visit."""
+    w = small(seed=31, n=n, sizes=((70, 50), (33, 64)))
+    rng = np.random.default_rng(n)
+    w.scene.opacity_logit[...] = rng.choice(np.float32([3.0, 3.85, 3.95, 4.6, 8.0]), n)
+    r = renderer_for(w, tile=tile, ppt=ppt, wave_w=sw)
+    P = DeviceParams.from_scene(w.scene)
+    G = _up(w, 3)
+    r.forward(P)
+    grads = DeviceParams.zeros_like(P)
+    r.backward(P, torch.from_numpy(G).cuda(), 0, grads)
+    torch.cuda.synchronize()
+    rep = grad_report(flat_grads(grads), oracle.backward(w.scene, w.cams, G, mode=0))
+    assert rep["fail"] == 0
+
+
 @pytest.mark.parametrize("tile,ppt,sw,schedule", [((16, 16), 4, 16, 0), ((32, 32), 2, 32, 1), ((32, 16), 4, 32, 0),
                                                    ((16, 8), 2, 16, 1), ((32, 32), 4, 16, 0), ((32, 16), 2, 16, 1),
                                                    ((32, 32), 4, 16, 2), ((16, 16), 2, 16, 3), ((8, 8), 1, 8, 3)])
