@@ -365,10 +365,6 @@ gs_status gs_project(gs_ctx c, const gs_params* params, const gs_camera* cams, i
   if ((s = check_params(c, params, "gs_project")) != GS_OK) return s;
   if (!cams) return fail(c, GS_ERR_INVALID, "gs_project: null cameras");
   const Plan& pl = c->plan;
-  if (v0 == 0) {   // a new step starts: clear the sticky overflow flag
-    Counters* ctr = seg<Counters>(ws, pl.ws.counters);
-    GS_HIP(c, launch_fill_u32(&ctr->overflow, 0u, 1, st));
-  }
   GS_HIP(c, timed(c, ST_PROJECT, st, [&] { return launch_project(pl, ptrs(params), cams, v0, nv, ws, st); }));
   return GS_OK;
 }

@@ -229,7 +229,9 @@ __device__ __forceinline__ ViewD read_view_d(const ViewD* vds, int v) {
 
 // One thread per view of the launch: the camera in double precision and the
 // guard-band limits kGuard (width / 2) / fx, kGuard (height / 2) / fy.
-__global__ void k_view_consts(const gs_camera* cams, int v0, int nv, ViewD* out) {
+// The launch that starts a step also clears its overflow flag (`clear`).
+__global__ void k_view_consts(const gs_camera* cams, int v0, int nv, ViewD* out, uint32_t* clear) {
+  if (clear && threadIdx.x == 0 && blockIdx.x == 0) *clear = 0u;
   const int v = v0 + (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (v >= v0 + nv) return;
   const gs_camera cam = cams[v];
@@ -626,9 +628,12 @@ hipError_t launch_project(const Plan& pl, const ParamPtrs& p, const gs_camera* c
   a.cell_mask = pl.cell_mask;
   a.cell_row = pl.cell_row;
   const int blocks = (p.n + 63) / 64;
-  if (blocks == 0) return hipSuccess;
   if (nv < 1 || v0 < 0 || v0 + nv > kMaxViews) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_view_consts, dim3(1), dim3(kMaxViews), 0, st, cams, v0, nv, seg<ViewD>(ws, pl.ws.vconst));
+  if (blocks == 0)
+    return v0 == 0 ? launch_fill_u32(&seg<Counters>(ws, pl.ws.counters)->overflow, 0u, 1, st) : hipSuccess;
+  // (the sticky overflow flag is cleared where a new step starts)
+  hipLaunchKernelGGL(k_view_consts, dim3(1), dim3(kMaxViews), 0, st, cams, v0, nv, seg<ViewD>(ws, pl.ws.vconst),
+                     v0 == 0 ? &seg<Counters>(ws, pl.ws.counters)->overflow : nullptr);
   const dim3 block(64 * kViewWaves);
   switch (p.deg) {
     case 0: hipLaunchKernelGGL(k_project<0>, dim3(blocks), block, 0, st, a); break;
@@ -662,7 +667,8 @@ hipError_t launch_project_bwd(const Plan& pl, const ParamPtrs& p, const gs_camer
   const int blocks = (grads.n + 63) / 64;
   if (blocks == 0) return hipSuccess;
   if (nv < 1 || v0 < 0 || v0 + nv > kMaxViews) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_view_consts, dim3(1), dim3(kMaxViews), 0, st, cams, v0, nv, seg<ViewD>(ws, pl.ws.vconst));
+  hipLaunchKernelGGL(k_view_consts, dim3(1), dim3(kMaxViews), 0, st, cams, v0, nv, seg<ViewD>(ws, pl.ws.vconst),
+                     nullptr);
   const dim3 block(64 * kViewWaves);
   switch (p.deg) {
     case 0: hipLaunchKernelGGL(k_project_bwd<0>, dim3(blocks), block, 0, st, a); break;

@@ -263,12 +263,37 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t value, int64_t count) {
 // chunk].
 constexpr int kHistCopies = 4;
 
+// Sorts of up to kDirectChunks chunks scan no histogram: it is stored chunk by
+// chunk instead of digit by digit, and each scatter workgroup adds up the rows
+// of the chunks before its own itself (coalesced, from L2).  The scan costs two
+// launches of 4 to 5 us a pass however few chunks there are; the rows cost a
+// workgroup about 1 us per 32 chunks.
+constexpr int64_t kDirectChunks = 192;
+
+__device__ __forceinline__ int64_t hist_at(uint32_t digit, uint32_t chunk, int64_t nblocks, bool direct) {
+  return direct ? (int64_t)chunk * 256 + digit : (int64_t)digit * nblocks + chunk;
+}
+
+// Global start of digit threadIdx.x's run of chunk blockIdx.x, from the
+// unscanned rows of `chunks` chunks; *all receives the keys of all of them.
+__device__ __forceinline__ uint32_t direct_digit_base(const uint32_t* hist, uint32_t chunks, uint32_t* s_tmp,
+                                                      uint32_t* all) {
+  uint32_t before = 0, total = 0;
+#pragma unroll 16
+  for (uint32_t c = 0; c < chunks; ++c) {
+    const uint32_t x = hist[(size_t)c * 256 + threadIdx.x];
+    before += c < blockIdx.x ? x : 0u;
+    total += x;
+  }
+  return block_excl_scan(total, s_tmp, all) + before;
+}
+
 // With `valid` (the first depth pass, reading the dense (view, Gaussian)
 // arrays), key k counts only where valid[k] != 0: the pass then compacts the
 // visible pairs as it sorts them.
 __global__ __launch_bounds__(B) void k_radix_hist(const uint32_t* keys, const uint32_t* valid, int64_t max_count,
                                                   const uint32_t* dcount, int shift, uint32_t dmask, int64_t nblocks,
-                                                  uint32_t* hist) {
+                                                  uint32_t* hist, bool direct) {
   __shared__ uint32_t h[NW][256][kHistCopies];
 #pragma unroll
   for (int q = 0; q < NW * kHistCopies; ++q) (&h[0][0][0])[q * 256 + threadIdx.x] = 0;
@@ -295,7 +320,7 @@ __global__ __launch_bounds__(B) void k_radix_hist(const uint32_t* keys, const ui
   for (int q = 0; q < NW; ++q)
 #pragma unroll
     for (int k = 0; k < kHistCopies; ++k) t += h[q][threadIdx.x][k];
-  if (chunk < nblocks) hist[(int64_t)threadIdx.x * nblocks + chunk] = t;
+  if (chunk < nblocks) hist[hist_at(threadIdx.x, (uint32_t)chunk, nblocks, direct)] = t;
 }
 
 // Scatter of one chunk (kSortChunk keys, split into NW contiguous wavefront
@@ -407,8 +432,9 @@ template <bool kPay, bool kDense = false>
 __global__ __launch_bounds__(B) void k_radix_scatter(const uint32_t* kin, const uint32_t* vin, uint32_t* kout,
                                                      uint32_t* vout, const uint2* pin, uint2* pout,
                                                      int64_t max_count, const uint32_t* dcount, int shift,
-                                                     uint32_t dmask, int64_t nblocks, const uint32_t* hist_scanned,
-                                                     const uint32_t* valid = nullptr, uint32_t value_base = 0) {
+                                                     uint32_t dmask, int64_t nblocks, const uint32_t* hist, bool direct,
+                                                     const uint32_t* valid = nullptr, uint32_t value_base = 0,
+                                                     uint32_t* taken_out = nullptr) {
   __shared__ __align__(16) uint32_t s_kv[2 * kSortChunk];   // keys | values, later the payload
   __shared__ uint32_t s_wc[NW][256];
   __shared__ uint32_t s_gbase[256];
@@ -436,7 +462,7 @@ __global__ __launch_bounds__(B) void k_radix_scatter(const uint32_t* kin, const 
   const uint32_t lane0 = (uint32_t)w * kWaveKeys + (uint32_t)lane;
   // this chunk's global start of digit threadIdx.x, needed only after the
   // ranking: loaded with the keys so that its latency overlaps theirs
-  const uint32_t digit_base = hist_scanned[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+  uint32_t digit_base = direct ? 0u : hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
   if (cnt == (uint32_t)kSortChunk) {   // uniform
 #pragma unroll
     for (int r = 0; r < kWaveRounds; ++r) {
@@ -481,6 +507,11 @@ __global__ __launch_bounds__(B) void k_radix_scatter(const uint32_t* kin, const 
       val[r] = value_base + (uint32_t)(begin + li);
     }
     in_mask |= in ? 1u << r : 0u;
+  }
+  if (direct) {   // uniform
+    uint32_t all;
+    digit_base = direct_digit_base(hist, (n + kSortChunk - 1) / kSortChunk, s_tmp, &all);
+    if (kDense && blockIdx.x == 0 && threadIdx.x == 0) *taken_out = all;
   }
   __syncthreads();
   uint32_t pos[kWaveRounds];
@@ -659,7 +690,8 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
                                                   const uint32_t* total_keys, const uint2* sorted_rect,
                                                   const ViewInfo* views, int32_t n_views, int64_t n_gauss,
                                                   int32_t tile_begin, uint32_t cap, int64_t nblocks, uint32_t dmask0,
-                                                  uint32_t* hist) {
+                                                  uint32_t* hist, bool direct, Counters* ctr, uint2* ranges,
+                                                  int64_t ntiles) {
   __shared__ int32_t s_diff[257];
   __shared__ uint32_t s_full;
   __shared__ uint32_t s_tmp[NW];
@@ -673,6 +705,17 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
   for (int v = threadIdx.x; v < n_views; v += B) s_view[v] = make_int2(views[v].tile_base - tile_begin, views[v].tiles_x);
   __syncthreads();
   const uint32_t all_keys = *total_keys;
+  // on the side (launches of their own would cost 4 us each): the build's key
+  // count and overflow flag, and empty ranges for the tiles
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ctr->key_cap = cap;
+    if (all_keys > cap) {
+      ctr->overflow = 1u;
+      ctr->overflow_any = 1u;
+    }
+  }
+  for (int64_t t = (int64_t)blockIdx.x * B + threadIdx.x; t < ntiles; t += (int64_t)gridDim.x * B)
+    ranges[t] = make_uint2(0u, 0u);
   const uint32_t n = min(all_keys, cap);
   const uint32_t M = dmask0 + 1u;
   const int bits0 = __popc(dmask0);
@@ -740,7 +783,7 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
   const int32_t x = d < M ? s_diff[d] : 0;
   uint32_t total;
   const uint32_t below = block_excl_scan((uint32_t)x, s_tmp, &total);
-  hist[(int64_t)d * nblocks + blockIdx.x] = d < M ? below + (uint32_t)x + s_full : 0u;
+  hist[hist_at(d, blockIdx.x, nblocks, direct)] = d < M ? below + (uint32_t)x + s_full : 0u;
 }
 
 // The tile sort's first pass fused with the key emission: workgroup c walks
@@ -756,7 +799,7 @@ __global__ __launch_bounds__(B) void k_emit_scatter(const uint32_t* sorted_vis, 
                                                     const uint32_t* total_keys, const uint2* sorted_rect,
                                                     const ViewInfo* views, int32_t n_views, int64_t n_gauss,
                                                     int32_t tile_begin, uint32_t cap, int64_t nblocks, uint32_t dmask0,
-                                                    const uint32_t* hist_scanned, uint32_t* kout, uint32_t* vout) {
+                                                    const uint32_t* hist, bool direct, uint32_t* kout, uint32_t* vout) {
   __shared__ __align__(16) uint32_t s_kv[2 * kSortChunk];   // keys | values
   __shared__ int2 s_view[kMaxViews];
   __shared__ union {   // the walk's staging, then the ranking's counters
@@ -770,6 +813,7 @@ __global__ __launch_bounds__(B) void k_emit_scatter(const uint32_t* sorted_vis, 
   } u;
   uint32_t* s_key = s_kv;
   uint32_t* s_val = s_kv + kSortChunk;
+  uint32_t* s_scan = s_kv;   // (free until the walk)
   const uint32_t all_keys = *total_keys;
   const uint32_t n = min(all_keys, cap);
   const uint64_t S0 = (uint64_t)blockIdx.x * kSortChunk;
@@ -778,7 +822,11 @@ __global__ __launch_bounds__(B) void k_emit_scatter(const uint32_t* sorted_vis, 
   const uint32_t cnt = S1 - (uint32_t)S0;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int v = threadIdx.x; v < n_views; v += B) s_view[v] = make_int2(views[v].tile_base - tile_begin, views[v].tiles_x);
-  const uint32_t digit_base = hist_scanned[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+  uint32_t digit_base = direct ? 0u : hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+  if (direct) {   // uniform
+    uint32_t all;
+    digit_base = direct_digit_base(hist, (n + kSortChunk - 1) / kSortChunk, s_scan, &all);
+  }
   __syncthreads();
   emit_walk(u.walk, sorted_vis, koff, firsts, *nvis_p, all_keys, sorted_rect, s_view, (uint32_t)n_gauss, S0, S1,
             [&](uint32_t slot, uint32_t key, uint32_t val) {
@@ -805,18 +853,6 @@ __global__ __launch_bounds__(B) void k_emit_scatter(const uint32_t* sorted_vis, 
   uint32_t dst[1];
   rank_and_write<false, true>(key, val, in_mask, digit_base, 0, dmask0, s_key, s_val, u.rank.wc, u.rank.gbase,
                               u.rank.tmp, u.rank.taken, kout, vout, pos, dst, n);
-}
-
-__global__ void k_key_total(Counters* c, const uint32_t* total_keys, uint32_t cap) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    const uint32_t k = *total_keys;
-    c->keys = k;
-    c->key_cap = cap;
-    if (k > cap) {
-      c->overflow = 1u;
-      c->overflow_any = 1u;
-    }
-  }
 }
 
 // Per-tile [start, end) of the sorted keys; thread q looks at keys 4q..4q+3
@@ -991,21 +1027,23 @@ static hipError_t radix_sort(const Plan& pl, void* ws, uint32_t* ka, uint32_t* v
     }
     if (nb > 0) {
       const uint32_t* dc = from_dense ? nullptr : dcount;
+      const bool direct = nb <= kDirectChunks;
       hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nb), dim3(B), 0, st, ki, from_dense ? dense->valid : nullptr,
-                         max_count, dc, shift, dmask, nb, hist);
+                         max_count, dc, shift, dmask, nb, hist, direct);
       // a dense pass's digit counts total the taken keys
-      hipError_t e = scan_src(ScanSrc{hist, nullptr, 0}, hist, 256 * nb, nullptr, partial, pl.ws.partial_len,
-                              from_dense ? dense->taken : nullptr, st);
+      hipError_t e = direct ? hipSuccess
+                            : scan_src(ScanSrc{hist, nullptr, 0}, hist, 256 * nb, nullptr, partial, pl.ws.partial_len,
+                                       from_dense ? dense->taken : nullptr, st);
       if (e != hipSuccess) return e;
       if (from_dense)
         hipLaunchKernelGGL((k_radix_scatter<true, true>), dim3((unsigned)nb), dim3(B), 0, st, ki, vi, ko, vo, pi, po,
-                           max_count, dc, shift, dmask, nb, hist, dense->valid, dense->value_base);
+                           max_count, dc, shift, dmask, nb, hist, direct, dense->valid, dense->value_base, dense->taken);
       else if (pa)
         hipLaunchKernelGGL((k_radix_scatter<true, false>), dim3((unsigned)nb), dim3(B), 0, st, ki, vi, ko, vo, pi,
-                           po, max_count, dc, shift, dmask, nb, hist, nullptr, 0u);
+                           po, max_count, dc, shift, dmask, nb, hist, direct, nullptr, 0u, nullptr);
       else
         hipLaunchKernelGGL((k_radix_scatter<false, false>), dim3((unsigned)nb), dim3(B), 0, st, ki, vi, ko, vo, pi,
-                           po, max_count, dc, shift, dmask, nb, hist, nullptr, 0u);
+                           po, max_count, dc, shift, dmask, nb, hist, direct, nullptr, 0u, nullptr);
     } else if (from_dense) {
       hipError_t e = launch_fill_u32(dense->taken, 0u, 1, st);
       if (e != hipSuccess) return e;
@@ -1061,8 +1099,6 @@ hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream
   e = scan_src(ScanSrc{reinterpret_cast<const uint32_t*>(sorted_rect), nullptr, 3}, koff, len, &ctr->nvis, partial,
                pl.ws.partial_len, &ctr->keys, st, firsts, (uint32_t)key_chunks);
   if (e != hipSuccess) return e;
-  // ctr->keys holds the total; record it and the overflow flag
-  hipLaunchKernelGGL(k_key_total, dim3(1), dim3(64), 0, st, ctr, &ctr->keys, cap);
   // 4. digit counts of the tile sort's first pass over the (tile, value)
   // pairs in depth order, one sort chunk per workgroup, and their scan
   const int32_t tile_begin = pl.views[v0].tile_base;
@@ -1076,21 +1112,23 @@ hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream
   const int first_bits = bits - 8 * ((bits - 1) / 8);
   uint32_t* hist = seg<uint32_t>(ws, pl.ws.hist);
   const uint32_t dmask0 = (1u << first_bits) - 1u;
+  const bool direct = key_chunks <= kDirectChunks;
   hipLaunchKernelGGL(k_emit_count, dim3((unsigned)key_chunks), dim3(B), 0, st, sorted_vis, koff, firsts, &ctr->nvis,
-                     &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N, tile_begin, cap, key_chunks, dmask0, hist);
-  e = scan_src(ScanSrc{hist, nullptr, 0}, hist, 256 * key_chunks, nullptr, partial, pl.ws.partial_len, nullptr, st);
-  if (e != hipSuccess) return e;
+                     &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N, tile_begin, cap, key_chunks, dmask0, hist, direct, ctr,
+                     ranges + tile_begin, ntiles);
+  if (!direct) {
+    e = scan_src(ScanSrc{hist, nullptr, 0}, hist, 256 * key_chunks, nullptr, partial, pl.ws.partial_len, nullptr, st);
+    if (e != hipSuccess) return e;
+  }
   // 5. stable sort by tile (relative to the first tile of the call): its
   // first pass fused with the emission, into the second buffers
   hipLaunchKernelGGL(k_emit_scatter, dim3((unsigned)key_chunks), dim3(B), 0, st, sorted_vis, koff, firsts, &ctr->nvis,
-                     &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N, tile_begin, cap, key_chunks, dmask0, hist, keys_b,
-                     vals_b);
+                     &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N, tile_begin, cap, key_chunks, dmask0, hist, direct,
+                     keys_b, vals_b);
   e = radix_sort(pl, ws, keys_a, vals_a, keys_b, vals_b, nullptr, nullptr, pl.cap, &ctr->keys, bits, &in_b, st, nullptr,
                  true, first_bits);
   if (e != hipSuccess) return e;
-  // 6. ranges
-  e = launch_fill_u32(reinterpret_cast<uint32_t*>(ranges + tile_begin), 0u, 2 * ntiles, st);
-  if (e != hipSuccess) return e;
+  // 6. ranges (empty ones were written with the digit counts)
   const uint32_t* sk = in_b ? keys_b : keys_a;
   // one quad of keys per thread (the loop in the kernel covers any size):
   // every wavefront's loads are in flight at once instead of one quad after
