@@ -268,7 +268,7 @@ constexpr int kHistCopies = 4;
 // of the chunks before its own itself (coalesced, from L2).  The scan costs two
 // launches of 4 to 5 us a pass however few chunks there are; the rows cost a
 // workgroup about 1 us per 32 chunks.
-constexpr int64_t kDirectChunks = 192;
+constexpr int64_t kDirectChunks = 320;
 
 __device__ __forceinline__ int64_t hist_at(uint32_t digit, uint32_t chunk, int64_t nblocks, bool direct) {
   return direct ? (int64_t)chunk * 256 + digit : (int64_t)digit * nblocks + chunk;
@@ -947,6 +947,174 @@ __global__ __launch_bounds__(256) void k_order_scatter(const uint2* ranges, uint
   if (t < ntiles) order[base[b] + r] = t;
 }
 
+// ---- tile lists of small models ----------------------------------------------
+// The sort's launches take 4 to 15 us each however little they hold: 17 of
+// them, 110 us, for a thousand Gaussians.  Where every pair can be compared
+// with every other of its view and every tile with every pair, three launches
+// build the same lists: k_small_rank gives each visible pair its place in its
+// view's depth order by counting the pairs before it, k_small_count counts for
+// each tile the pairs whose rectangle covers it, and k_small_fill writes them
+// in order behind those of the tiles before.
+constexpr uint32_t kInvisible = 0xffffffffu;   // above the bits of every depth
+// Bounds of that route: where it stops being the faster one (us per build,
+// compared / sorted, 16x16 tiles): 1000 Gaussians in one view of 64 tiles
+// 15 / 81; 8192 in 4 views of 676 tiles 64 / 123; 12,000 in 4 of 1764 113 / 144;
+// 16,000 in 4 of 676 157 / 125; 4096 in 1 of 8160 95 / 147; 3000 in 4 of 14,400
+// 147 / 152; 24,000 in 1 of 361 115 / 117.
+constexpr int64_t kSmallN = 16384;                 // Gaussians
+constexpr int64_t kSmallCompares = 1ll << 29;      // compares of the ranking, all views
+constexpr int64_t kSmallCovers = 1ll << 25;        // (tile, Gaussian) pairs
+
+// A workgroup ranks 64 pairs of a view, its kRankWaves wavefronts counting an
+// equal part of the view's pairs each (one compare and one add of the carry
+// per pair): 8 cycles per 64 compares, so a view of 8192 takes 16 wavefronts
+// 2 us of each SIMD, where four would leave half of the chip idle for 8 us.
+// Ties go by index.
+constexpr int kRankWaves = 16;
+
+__global__ __launch_bounds__(64 * kRankWaves) void k_small_rank(const uint32_t* depth, const uint32_t* count, const uint2* rect,
+                                                  uint32_t n, uint32_t pair0, uint32_t* sorted_vis, uint2* sorted_rect,
+                                                  uint32_t* view_count) {
+  __shared__ uint32_t s_key[kRankWaves][64];
+  __shared__ uint32_t s_rank[kRankWaves][64];
+  __shared__ uint32_t s_valid[kRankWaves];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const size_t v0 = (size_t)blockIdx.y * n;   // the view's first pair
+  const uint32_t i = blockIdx.x * 64u + (uint32_t)lane;
+  const bool mine = i < n && count[v0 + i] != 0u;
+  const uint32_t key = mine ? depth[v0 + i] : kInvisible;
+  const uint32_t part = ((n + kRankWaves - 1) / kRankWaves + 63u) & ~63u;
+  const uint32_t j0 = (uint32_t)w * part, j1 = min(n, j0 + part);
+  uint32_t rank = 0, valid = 0;
+  uint32_t nk = kInvisible;
+  if (j0 + (uint32_t)lane < j1 && count[v0 + j0 + lane] != 0u) nk = depth[v0 + j0 + lane];
+  for (uint32_t j = j0; j < j1; j += 64u) {
+    const uint32_t kj = nk;
+    nk = kInvisible;
+    const uint32_t jn = j + 64u + (uint32_t)lane;   // the next 64, in flight meanwhile
+    if (jn < j1 && count[v0 + jn] != 0u) nk = depth[v0 + jn];
+    valid += (uint32_t)__popcll(__ballot(kj != kInvisible));
+    s_key[w][lane] = kj;
+    __builtin_amdgcn_wave_barrier();
+    if (j + 64u <= blockIdx.x * 64u) {   // uniform: all before this workgroup's pairs
+#pragma unroll
+      for (int q = 0; q < 64; ++q) rank += s_key[w][q] <= key ? 1u : 0u;
+    } else if (j >= blockIdx.x * 64u + 64u) {
+#pragma unroll
+      for (int q = 0; q < 64; ++q) rank += s_key[w][q] < key ? 1u : 0u;
+    } else {
+      for (int q = 0; q < 64; ++q) {
+        const uint32_t x = s_key[w][q];
+        rank += x < key || (x == key && j + (uint32_t)q < i) ? 1u : 0u;
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  s_rank[w][lane] = rank;
+  if (lane == 0) s_valid[w] = valid;
+  __syncthreads();
+  if (w != 0) return;
+  rank = 0;
+  valid = 0;
+#pragma unroll
+  for (int q = 0; q < kRankWaves; ++q) {
+    rank += s_rank[q][lane];
+    valid += s_valid[q];
+  }
+  if (blockIdx.x == 0 && lane == 0) view_count[blockIdx.y] = valid;
+  if (mine) {
+    sorted_vis[v0 + rank] = pair0 + (uint32_t)v0 + i;
+    sorted_rect[v0 + rank] = rect[v0 + i];
+  }
+}
+
+// The part of a tile's pairs that wavefront w looks at, in depth order.
+struct SmallTile {
+  uint32_t tx, ty;
+  size_t first;        // the view's first pair
+  uint32_t k0, k1;     // the wavefront's pairs of the view
+  __device__ __forceinline__ SmallTile(const ViewInfo* views, const int32_t* tile_view, int32_t tile, int32_t v0,
+                                       uint32_t n, const uint32_t* view_count, int w) {
+    const int32_t v = tile_view[tile];
+    const ViewInfo view = views[v];
+    const uint32_t local = (uint32_t)(tile - view.tile_base);
+    ty = local / (uint32_t)view.tiles_x;
+    tx = local - ty * (uint32_t)view.tiles_x;
+    first = (size_t)(v - v0) * n;
+    const uint32_t nvis = view_count[v - v0], quarter = ((nvis + NW - 1) / NW + 63u) & ~63u;
+    k0 = min(nvis, (uint32_t)w * quarter);
+    k1 = min(nvis, k0 + quarter);
+  }
+  __device__ __forceinline__ bool covers(const uint2* sorted_rect, uint32_t k) const {
+    if (k >= k1) return false;
+    const uint2 r = sorted_rect[first + k];
+    return tx >= (r.x & 0xffffu) && ty >= (r.x >> 16) && tx <= (r.y & 0xffffu) && ty <= (r.y >> 16);
+  }
+};
+
+// tile_count[t][w]: pairs of tile t among wavefront w's.
+__global__ __launch_bounds__(B) void k_small_count(const ViewInfo* views, const int32_t* tile_view, int32_t tile_begin,
+                                                   int32_t v0, uint32_t n, const uint32_t* view_count,
+                                                   const uint2* sorted_rect, uint32_t* tile_count) {
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const SmallTile t(views, tile_view, tile_begin + (int32_t)blockIdx.x, v0, n, view_count, w);
+  uint32_t c = 0;
+#pragma unroll 4
+  for (uint32_t k = t.k0; k < t.k1; k += 64u) c += (uint32_t)__popcll(__ballot(t.covers(sorted_rect, k + lane)));
+  if (lane == 0) tile_count[blockIdx.x * NW + w] = c;
+}
+
+__global__ __launch_bounds__(B) void k_small_fill(const ViewInfo* views, const int32_t* tile_view, int32_t tile_begin,
+                                                  int32_t v0, int32_t nv, uint32_t n, const uint32_t* view_count,
+                                                  const uint32_t* sorted_vis, const uint2* sorted_rect,
+                                                  const uint32_t* tile_count, uint32_t cap, uint32_t* vals,
+                                                  uint2* ranges, Counters* ctr) {
+  __shared__ uint32_t s_tmp[NW];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+  uint32_t before = 0;
+  for (uint32_t q = threadIdx.x; q < blockIdx.x; q += B) {
+    const uint4 c = reinterpret_cast<const uint4*>(tile_count)[q];
+    before += (c.x + c.y) + (c.z + c.w);
+  }
+  static_assert(NW == 4, "a tile's counts are read as one uint4");
+  uint32_t base;
+  block_excl_scan(before, s_tmp, &base);
+  uint32_t cnt[NW], at = base, all = 0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    cnt[q] = tile_count[blockIdx.x * NW + q];
+    at += q < w ? cnt[q] : 0u;
+    all += cnt[q];
+  }
+  if (threadIdx.x == 0)
+    ranges[blockIdx.x] = all ? make_uint2(min(base, cap), min(base + all, cap)) : make_uint2(0u, 0u);
+  const SmallTile t(views, tile_view, tile_begin + (int32_t)blockIdx.x, v0, n, view_count, w);
+#pragma unroll 4
+  for (uint32_t k = t.k0; k < t.k1; k += 64u) {
+    const bool in = t.covers(sorted_rect, k + lane);
+    const uint64_t m = __ballot(in);
+    const uint32_t d = at + (uint32_t)__popcll(m & lt_mask);
+    if (in && d < cap) vals[d] = sorted_vis[t.first + k + lane];
+    at += (uint32_t)__popcll(m);
+  }
+  if (blockIdx.x == gridDim.x - 1 && w == 0) {   // the totals
+    uint32_t nvis = 0;
+    for (int32_t v = lane; v < nv; v += 64) nvis += view_count[v];
+    nvis = wave_incl_scan(nvis);
+    if (lane == 63) {
+      const uint32_t keys = base + all;
+      ctr->nvis = nvis;
+      ctr->keys = keys;
+      ctr->key_cap = cap;
+      if (keys > cap) {
+        ctr->overflow = 1u;
+        ctr->overflow_any = 1u;
+      }
+    }
+  }
+}
+
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 }  // namespace
@@ -1059,6 +1227,28 @@ hipError_t launch_sort_pairs(const Plan& pl, void* ws, uint32_t* ka, uint32_t* v
   return radix_sort(pl, ws, ka, va, kb, vb, nullptr, nullptr, count, nullptr, bits, in_b, st);
 }
 
+// Longest-first order of the call's tiles for the persistent compositing kernels.
+static hipError_t order_tiles(const Plan& pl, void* ws, int32_t tile_begin, int64_t ntiles, hipStream_t st) {
+  if (pl.schedule == 3 && ntiles > 0) {
+    const uint2* ranges = seg<uint2>(ws, pl.ws.ranges) + tile_begin;
+    uint32_t* bkt = seg<uint32_t>(ws, pl.ws.obucket);
+    const hipError_t e = launch_fill_u32(bkt, 0u, 2 * kOrderBuckets, st);
+    if (e != hipSuccess) return e;
+    const unsigned ob = (unsigned)cdiv(ntiles, 256);
+    hipLaunchKernelGGL(k_order_hist, dim3(ob), dim3(256), 0, st, ranges, (uint32_t)ntiles, bkt);
+    hipLaunchKernelGGL(k_order_scatter, dim3(ob), dim3(256), 0, st, ranges, (uint32_t)ntiles, bkt,
+                       seg<uint32_t>(ws, pl.ws.order));
+  }
+  return hipGetLastError();
+}
+
+// Whether the call's lists are built by comparing everything with everything.
+static bool small_lists(const Plan& pl, int nv, int64_t ntiles) {
+  const int64_t n = pl.n;
+  return n <= kSmallN && n * n * nv <= kSmallCompares && n * ntiles <= kSmallCovers &&
+         16 * ntiles <= (int64_t)(pl.ws.vals_a - pl.ws.vrect_b);   // the tile counts' scratch
+}
+
 hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream_t st) {
   Counters* ctr = seg<Counters>(ws, pl.ws.counters);
   const int64_t N = pl.n;
@@ -1081,6 +1271,22 @@ hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream
   const uint32_t cap = (uint32_t)pl.cap;
   hipError_t e;
   if (len == 0) return hipSuccess;
+  const int32_t tile_begin = pl.views[v0].tile_base;
+  const int32_t tile_end = (v0 + nv < pl.n_views) ? pl.views[v0 + nv].tile_base : pl.total_tiles;
+  const int64_t ntiles = tile_end - tile_begin;
+  if (small_lists(pl, nv, ntiles)) {
+    uint32_t* view_count = seg<uint32_t>(ws, pl.ws.hist);
+    uint32_t* tile_count = reinterpret_cast<uint32_t*>(vrect_b);   // up to the values, all of it free here
+    uint32_t* vals = sorted_values_in_b(pl, v0, nv) ? vals_b : vals_a;
+    hipLaunchKernelGGL(k_small_rank, dim3((unsigned)cdiv(N, 64), (unsigned)nv), dim3(64 * kRankWaves), 0, st, depth + base,
+                       count + base, seg<uint2>(ws, pl.ws.rect) + base, (uint32_t)N, (uint32_t)base, vis_a, vrect_a,
+                       view_count);
+    hipLaunchKernelGGL(k_small_count, dim3((unsigned)ntiles), dim3(B), 0, st, pl.d_views, pl.d_tile_view, tile_begin,
+                       v0, (uint32_t)N, view_count, vrect_a, tile_count);
+    hipLaunchKernelGGL(k_small_fill, dim3((unsigned)ntiles), dim3(B), 0, st, pl.d_views, pl.d_tile_view, tile_begin, v0,
+                       nv, (uint32_t)N, view_count, vis_a, vrect_a, tile_count, cap, vals, ranges + tile_begin, ctr);
+    return order_tiles(pl, ws, tile_begin, ntiles, st);
+  }
   // 1-2. stable depth sort of the visible pairs (ties keep (view, Gaussian)
   // order); its first pass reads the dense (view, Gaussian) arrays and takes
   // the visible pairs only, so it also compacts them and counts them into
@@ -1101,11 +1307,8 @@ hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream
   if (e != hipSuccess) return e;
   // 4. digit counts of the tile sort's first pass over the (tile, value)
   // pairs in depth order, one sort chunk per workgroup, and their scan
-  const int32_t tile_begin = pl.views[v0].tile_base;
-  const int32_t tile_end = (v0 + nv < pl.n_views) ? pl.views[v0 + nv].tile_base : pl.total_tiles;
   // tile bits of the call, split into passes of 8 bits with the remainder
   // taken first: fewer digits in the first pass
-  const int64_t ntiles = tile_end - tile_begin;
   int bits = 0;
   while ((1ll << bits) < ntiles) ++bits;
   if (bits == 0) bits = 1;
@@ -1135,17 +1338,7 @@ hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream
   // another per thread
   const int64_t rblocks = cdiv(cdiv(pl.cap, 4), 256) < 0x7fffffffll ? cdiv(cdiv(pl.cap, 4), 256) : 0x7fffffffll;
   hipLaunchKernelGGL(k_ranges, dim3((unsigned)rblocks), dim3(256), 0, st, sk, &ctr->keys, cap, tile_begin, ranges);
-  // 7. longest-first order of the call's tiles for the persistent compositing kernels
-  if (pl.schedule == 3 && ntiles > 0) {
-    uint32_t* bkt = seg<uint32_t>(ws, pl.ws.obucket);
-    e = launch_fill_u32(bkt, 0u, 2 * kOrderBuckets, st);
-    if (e != hipSuccess) return e;
-    const unsigned ob = (unsigned)cdiv(ntiles, 256);
-    hipLaunchKernelGGL(k_order_hist, dim3(ob), dim3(256), 0, st, ranges + tile_begin, (uint32_t)ntiles, bkt);
-    hipLaunchKernelGGL(k_order_scatter, dim3(ob), dim3(256), 0, st, ranges + tile_begin, (uint32_t)ntiles, bkt,
-                       seg<uint32_t>(ws, pl.ws.order));
-  }
-  return hipGetLastError();
+  return order_tiles(pl, ws, tile_begin, ntiles, st);
 }
 
 }  // namespace gs

@@ -111,6 +111,42 @@ def test_tile_lists_with_narrow_first_digit_bit_exact(oracle, sizes):
     assert np.array_equal(ranges, ranges_o)
 
 
+@pytest.mark.parametrize("n,sizes,tile", [
+    (1, ((64, 48),), (16, 16)), (64, ((33, 64),), (8, 8)), (65, ((70, 50), (33, 64)), (16, 16)),
+    (1025, ((40, 40),) * 25, (16, 8)), (16384, ((240, 128),), (8, 8)),       # compared
+    (16385, ((240, 128),), (8, 8)), (16385, ((264, 128),), (8, 8)),          # sorted: too many Gaussians
+    (1500, ((1280, 720), (640, 360)), (8, 8)),                               # sorted: 1500 x 18,000 tiles
+    (8200, ((64, 48),) * 8, (16, 16))])                                      # sorted: compares of 8 views
+def test_tile_lists_either_side_of_the_small_model_bounds(oracle, n, sizes, tile):
+    """The lists of the comparing and of the sorting route, bit-exact at wave,
+    part and bound edges, with equal depths (ties go by index)."""
+    w = small(seed=150, n=n, sizes=sizes)
+    rng = np.random.default_rng(n)
+    k = n // 3
+    if k:   # every third Gaussian shares its mean with another one
+        w.scene.mean[:, rng.permutation(n)[:k]] = w.scene.mean[:, rng.integers(0, n, k)]
+        w.scene.log_scale[:, :2] = -0.5
+    r = renderer_for(w, tile=tile, cap=1 << 22)
+    P = DeviceParams.from_scene(w.scene)
+    r.forward(P)
+    c = r.counters()
+    vals_o, ranges_o = oracle.tile_lists(w.scene, w.cams, *tile)
+    assert c.overflow == 0 and c.keys == len(vals_o)
+    assert c.visible == int((seg_np(r, "count", np.uint32) > 0).sum())
+    assert np.array_equal(seg_np(r, "sorted_values", np.uint32)[:c.keys], vals_o)
+    assert np.array_equal(seg_np(r, "ranges", np.uint32).reshape(-1, 2), ranges_o)
+
+
+def test_small_model_overflow_is_reported():
+    w = small(seed=102)
+    r = renderer_for(w, cap=100)
+    P = DeviceParams.from_scene(w.scene)
+    r.ctx.project(P, r.dev_cams, 0, r.n_views, r.ws)
+    r.ctx.build_tile_lists(0, r.n_views, r.ws)
+    c = r.counters()
+    assert c.overflow == 1 and c.keys > 100 and r.capacity_exceeded
+
+
 @pytest.mark.parametrize("bg", [(0.0, 0.0, 0.0), (0.3, 0.5, 0.1)])
 def test_composite_matches_oracle(oracle, bg):
     w = small(seed=103)
