@@ -123,7 +123,9 @@ WsLayout make_layout(int64_t n, int64_t nviews, int64_t tiles, int64_t pixels, i
   L.hist_blocks = cdiv(maxsort, kSortChunk);
   L.dblocks = (int32_t)cdiv(n, 256);
   int64_t maxscan = maxsort;
-  if (256 * L.hist_blocks > maxscan) maxscan = 256 * L.hist_blocks;
+  // (the tile sort's second pass: every one of 256 buckets may add a chunk)
+  const int64_t hist_len = 256 * (L.hist_blocks + 256);
+  if (hist_len > maxscan) maxscan = hist_len;
   if (6ll * L.dblocks > maxscan) maxscan = 6ll * L.dblocks;
   L.partial_len = cdiv(maxscan, kSortChunk) + 2;
   size_t o = 0;
@@ -146,7 +148,8 @@ WsLayout make_layout(int64_t n, int64_t nviews, int64_t tiles, int64_t pixels, i
   L.vals_a = take(4 * cap);
   L.vals_b = take(4 * cap);
   L.strips = take(4 * (size_t)cap);
-  L.hist = take(4 * (256 * L.hist_blocks + 1));
+  L.hist = take(4 * (hist_len + 1));
+  L.buckets = take(4 * 2 * 257);
   L.firsts = take(4 * L.hist_blocks);
   L.partial = take(4 * L.partial_len);
   L.ranges = take(8 * tiles);

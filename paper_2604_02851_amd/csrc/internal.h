@@ -12,8 +12,8 @@ namespace gs {
 constexpr int kMaxViews = 256;
 constexpr int kRecFloats = 12;    // splat record: 3 x float4
 constexpr int kG2Fields = 9;      // screen-space gradient fields per (view, Gaussian), one plane each
-constexpr int kSortBlock = 256;   // threads of the sort / scan kernels
-constexpr int kSortItems = 16;    // keys per thread per chunk
+constexpr int kSortBlock = 512;   // threads of the sort / scan kernels
+constexpr int kSortItems = 8;     // keys per thread per chunk
 constexpr int kSortChunk = kSortBlock * kSortItems;
 
 // Thresholds of the compositing rule, as FP32 values.
@@ -68,7 +68,8 @@ struct WsLayout {
   size_t koff;        // u32 [VN+1] key offsets in depth order
   size_t keys_a, keys_b, vals_a, vals_b;  // u32 [cap]
   size_t strips;      // u32 [cap] strip bits of each list entry, stored by the forward compositing
-  size_t hist;        // u32 [256 * max_blocks + 1]
+  size_t hist;        // u32 [256 * (max_blocks + 256) + 1]
+  size_t buckets;     // u32 [2 * 257] first keys and chunks of the tile sort's buckets
   size_t firsts;      // u32 [max_blocks] depth-order pair owning the first key slot of each sort chunk
   size_t partial;     // u32 [scan partials]
   size_t ranges;      // u32x2 [tiles]

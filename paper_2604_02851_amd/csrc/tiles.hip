@@ -8,7 +8,13 @@
 // pairs (a few per Gaussian) are sorted by depth first, keys are emitted in
 // that order, and a stable sort on the tile bits alone finishes the job:
 // 4 passes over the visible pairs plus ceil(tile bits / 8) passes over the
-// keys, instead of ~7 passes over the keys.
+// keys, instead of ~7 passes over the keys.  Tile ids of up to 16 bits are
+// sorted from their high half down: the first pass (fused with the emission)
+// leaves the keys in up to 256 buckets, of which only the low byte goes on,
+// and the second, inside the buckets, writes values alone and reads the tiles'
+// ranges off its digit starts.  From the low digit up, with whole keys, the two
+// passes, their counts and the range extraction of 58M keys took 0.82 ms
+// instead of 0.59.
 //
 // All kernels are driven by device-side counts so the stage can be captured
 // in a graph: grids are sized for the plan's capacity and idle blocks exit.
@@ -19,7 +25,7 @@ namespace {
 
 constexpr int B = kSortBlock;
 constexpr int NW = B / 64;
-static_assert(B == 256, "one thread per radix digit");
+static_assert(B >= 256 && B % 256 == 0, "at least one thread per radix digit");
 
 __device__ __forceinline__ uint32_t dev_count(const uint32_t* dcount, int64_t max_count) {
   if (!dcount) return (uint32_t)max_count;
@@ -37,7 +43,8 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
   return x;
 }
 
-// Exclusive scan over the block (B threads); *total receives the block sum.
+// Exclusive scan over the block (W wavefronts); *total receives the block sum.
+template <int W = NW>
 __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* s_wave, uint32_t* total) {
   const uint32_t inc = wave_incl_scan(x);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -45,7 +52,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* s_wave
   __syncthreads();
   uint32_t pre = 0, tot = 0;
 #pragma unroll
-  for (int k = 0; k < NW; ++k) {
+  for (int k = 0; k < W; ++k) {
     const uint32_t s = s_wave[k];
     pre += (k < w) ? s : 0u;
     tot += s;
@@ -261,7 +268,7 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t value, int64_t count) {
 // keys) then meets at most 64 / kHistCopies lanes of one wavefront at each
 // address instead of 64.  Counts are stored digit-major, hist[d * nblocks +
 // chunk].
-constexpr int kHistCopies = 4;
+constexpr int kHistCopies = 1024 / B;
 
 // Sorts of up to kDirectChunks chunks scan no histogram: it is stored chunk by
 // chunk instead of digit by digit, and each scatter workgroup adds up the rows
@@ -279,6 +286,7 @@ __device__ __forceinline__ int64_t hist_at(uint32_t digit, uint32_t chunk, int64
 __device__ __forceinline__ uint32_t direct_digit_base(const uint32_t* hist, uint32_t chunks, uint32_t* s_tmp,
                                                       uint32_t* all) {
   uint32_t before = 0, total = 0;
+  if (threadIdx.x >= 256) chunks = 0;
 #pragma unroll 16
   for (uint32_t c = 0; c < chunks; ++c) {
     const uint32_t x = hist[(size_t)c * 256 + threadIdx.x];
@@ -296,7 +304,7 @@ __global__ __launch_bounds__(B) void k_radix_hist(const uint32_t* keys, const ui
                                                   uint32_t* hist, bool direct) {
   __shared__ uint32_t h[NW][256][kHistCopies];
 #pragma unroll
-  for (int q = 0; q < NW * kHistCopies; ++q) (&h[0][0][0])[q * 256 + threadIdx.x] = 0;
+  for (int q = 0; q < NW * kHistCopies * 256 / B; ++q) (&h[0][0][0])[q * B + threadIdx.x] = 0;
   __syncthreads();
   const uint32_t n = dev_count(dcount, max_count);
   const int w = threadIdx.x >> 6, copy = threadIdx.x & (kHistCopies - 1);
@@ -315,6 +323,7 @@ __global__ __launch_bounds__(B) void k_radix_hist(const uint32_t* keys, const ui
     }
   }
   __syncthreads();
+  if (threadIdx.x >= 256) return;
   uint32_t t = 0;
 #pragma unroll
   for (int q = 0; q < NW; ++q)
@@ -337,6 +346,9 @@ constexpr int kWaveKeys = kSortChunk / NW;
 constexpr int kWaveRounds = kWaveKeys / 64;
 constexpr int kOutRounds = kSortChunk / B;
 
+// The kernels of a sort hold their chunk in 512 threads of 8 keys: with 256 of
+// 16 a sort too short to fill the chip takes a quarter longer (a scatter of one
+// chunk per compute unit 12.7 instead of 10.4 us), a long one the same.
 // Steps 1-4 of a scatter for the keys a chunk's wavefronts hold (key[r] and
 // val[r] of lane l of wavefront w are chunk entry w kWaveKeys + r 64 + l;
 // bit r of in_mask says whether it takes part).  s_wc must be zero and
@@ -345,8 +357,10 @@ constexpr int kOutRounds = kSortChunk / B;
 // r B + threadIdx.x) serve a payload that follows the keys; returns the
 // number of keys taken.  With kBounded, positions at or past `limit` are not
 // written (a safeguard where the digit counts come from another kernel's
-// arithmetic rather than from the keys themselves).
-template <bool kPay, bool kBounded = false>
+// arithmetic rather than from the keys themselves).  kKeyBytes: the keys are
+// written whole (4), only their bits below the digit as one byte (1), or not
+// at all (0).
+template <bool kPay, bool kBounded = false, int kKeyBytes = 4>
 __device__ __forceinline__ uint32_t rank_and_write(const uint32_t (&key)[kWaveRounds], const uint32_t (&val)[kWaveRounds],
                                                    uint32_t in_mask, uint32_t digit_base, int shift, uint32_t dmask,
                                                    uint32_t* s_key, uint32_t* s_val, uint32_t (*s_wc)[256],
@@ -361,13 +375,19 @@ __device__ __forceinline__ uint32_t rank_and_write(const uint32_t (&key)[kWaveRo
   for (int r = 0; r < kWaveRounds; ++r) {
     const bool taking = (in_mask >> r) & 1u;
     const uint32_t digit = (key[r] >> shift) & dmask;
-    uint64_t match = __ballot(taking);
+    // lanes with this lane's digit, bit by bit: with s all ones where the bit
+    // is set and zero elsewhere, ~(ballot ^ s) are the lanes that agree
+    const uint64_t here = __ballot(taking);
+    uint32_t lo = (uint32_t)here, hi = (uint32_t)(here >> 32);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      const bool bit = (digit >> b) & 1u;
-      const uint64_t bb = __ballot(bit);
-      match &= bit ? bb : ~bb;
+      if (b >= 5 && (dmask >> b) == 0u) break;   // uniform: no digit has this bit
+      const int32_t s = __builtin_amdgcn_sbfe((int)digit, b, 1);
+      const uint64_t bb = __ballot(s != 0);
+      lo &= ~((uint32_t)bb ^ (uint32_t)s);
+      hi &= ~((uint32_t)(bb >> 32) ^ (uint32_t)s);
     }
+    const uint64_t match = ((uint64_t)hi << 32) | lo;
     const uint32_t below = (uint32_t)__popcll(match & lt_mask);
     const uint32_t before = taking ? s_wc[w][digit] : 0u;
     __builtin_amdgcn_wave_barrier();
@@ -382,19 +402,21 @@ __device__ __forceinline__ uint32_t rank_and_write(const uint32_t (&key)[kWaveRo
     uint32_t c[NW], tot = 0;
 #pragma unroll
     for (int q = 0; q < NW; ++q) {
-      c[q] = s_wc[q][d];
+      c[q] = d < 256 ? s_wc[q][d] : 0u;
       tot += c[q];
     }
     uint32_t all;
     const uint32_t lstart = block_excl_scan(tot, s_tmp, &all);
     if (d == 0) s_taken = all;
-    uint32_t run = lstart;
+    if (d < 256) {
+      uint32_t run = lstart;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) {
-      s_wc[q][d] = run;
-      run += c[q];
+      for (int q = 0; q < NW; ++q) {
+        s_wc[q][d] = run;
+        run += c[q];
+      }
+      s_gbase[d] = digit_base - lstart;
     }
-    s_gbase[d] = digit_base - lstart;
   }
   __syncthreads();
   // 3. local placement in digit order
@@ -416,7 +438,8 @@ __device__ __forceinline__ uint32_t rank_and_write(const uint32_t (&key)[kWaveRo
       const uint32_t k = s_key[i];
       const uint32_t d = s_gbase[(k >> shift) & dmask] + i;
       if (kBounded && d >= limit) continue;
-      kout[d] = k;
+      if constexpr (kKeyBytes == 4) kout[d] = k;
+      if constexpr (kKeyBytes == 1) reinterpret_cast<uint8_t*>(kout)[d] = (uint8_t)(k & ((1u << shift) - 1u));
       vout[d] = s_val[i];
       if constexpr (kPay) dst[r] = d;
     }
@@ -448,7 +471,7 @@ __global__ __launch_bounds__(B) void k_radix_scatter(const uint32_t* kin, const 
   const uint32_t cnt = (uint32_t)min((uint64_t)kSortChunk, (uint64_t)n - begin);
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
-  for (int q = 0; q < NW; ++q) s_wc[q][threadIdx.x] = 0;
+  for (int q = 0; q < NW * 256 / B; ++q) (&s_wc[0][0])[q * B + threadIdx.x] = 0;
   uint32_t key[kWaveRounds], val[kWaveRounds];
   uint2 pay[kPay ? kWaveRounds : 1];
   // Each pass reads its input once: streaming loads leave the cache to the
@@ -462,7 +485,7 @@ __global__ __launch_bounds__(B) void k_radix_scatter(const uint32_t* kin, const 
   const uint32_t lane0 = (uint32_t)w * kWaveKeys + (uint32_t)lane;
   // this chunk's global start of digit threadIdx.x, needed only after the
   // ranking: loaded with the keys so that its latency overlaps theirs
-  uint32_t digit_base = direct ? 0u : hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+  uint32_t digit_base = direct || threadIdx.x >= 256 ? 0u : hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
   if (cnt == (uint32_t)kSortChunk) {   // uniform
 #pragma unroll
     for (int r = 0; r < kWaveRounds; ++r) {
@@ -544,26 +567,10 @@ __global__ __launch_bounds__(B) void k_radix_scatter(const uint32_t* kin, const 
 // straddles a chunk boundary is produced in part by both workgroups.  Within
 // a group, lane l produces slot S + l in each round.  The pair owning a slot is found
 // without searching: each pair whose first slot falls in the round marks that
-// slot with its index, and an inclusive max-scan over the lanes (carried from
-// the previous round, and started at the last pair that began at or before
-// the chunk) hands every slot the last pair that started at or before it.
-// The slot's tile within the pair's rectangle comes from a float-reciprocal
+// slot, and the marks up to a slot (one ballot and a bit count per lane, added
+// to those of the rounds before) count the pairs that started by then.  The
+// slot's tile within the pair's rectangle comes from a float-reciprocal
 // quotient corrected to the exact integer one.
-
-// Inclusive max-scan over the 64 lanes (values >= -1).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp_max(int v) {
-  return max(v, __builtin_amdgcn_update_dpp(-1, v, CTRL, ROW_MASK, 0xf, false));
-}
-__device__ __forceinline__ int wave_incl_max(int v) {
-  v = dpp_max<0x111, 0xf>(v);   // row_shr:1
-  v = dpp_max<0x112, 0xf>(v);   // row_shr:2
-  v = dpp_max<0x114, 0xf>(v);   // row_shr:4
-  v = dpp_max<0x118, 0xf>(v);   // row_shr:8
-  v = dpp_max<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-  v = dpp_max<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
-  return v;
-}
 
 // One lane's pair of a group of 64 depth-sorted visible pairs: first and
 // end key slot, (view, Gaussian) index and tile rectangle as two words
@@ -588,11 +595,10 @@ __device__ __forceinline__ PairIn load_pair(const uint32_t* koff, const uint32_t
 
 // Per-wavefront staging of the walk: the current group of 64 pairs.
 struct WalkLds {
-  uint32_t off[NW][64];    // first key slot
-  uint32_t vi[NW][64];     // (view, Gaussian) index
-  uint2 rect[NW][64];      // tile rectangle, as loaded
-  uint32_t view[NW][64];
-  int32_t mark[NW][64];
+  // first key slot, (view, Gaussian) index, first key, width | the view's
+  // tiles per row << 16 (neither exceeds 2048)
+  uint4 pair[NW][64];
+  uint32_t mark[NW][64];
 };
 
 // The walk over chunk blockIdx.x of the key slots, [S0, S1): every slot is
@@ -604,11 +610,8 @@ __device__ __forceinline__ void emit_walk(WalkLds& L, const uint32_t* sorted_vis
                                           const uint32_t* firsts, uint32_t nvis, uint32_t all_keys,
                                           const uint2* sorted_rect, const int2* s_view, uint32_t ng, uint64_t S0,
                                           uint32_t S1, Emit emit) {
-  uint32_t (&s_off)[NW][64] = L.off;
-  uint32_t (&s_vi)[NW][64] = L.vi;
-  uint2 (&s_rect)[NW][64] = L.rect;
-  uint32_t (&s_v)[NW][64] = L.view;
-  int32_t (&s_mark)[NW][64] = L.mark;
+  uint4 (&s_pair)[NW][64] = L.pair;
+  uint32_t (&s_mark)[NW][64] = L.mark;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const float inv_ng = 1.f / (float)ng;
   // the wavefront takes every NW-th group of 64 pairs; each group's loads go
@@ -628,10 +631,10 @@ __device__ __forceinline__ void emit_walk(WalkLds& L, const uint32_t* sorted_vis
     const uint64_t lv = (uint64_t)v * ng;
     if (lv > vi) v -= 1u;
     else if (lv + ng <= vi) v += 1u;
-    s_vi[w][lane] = vi;
-    s_rect[w][lane] = cur.r;
-    s_v[w][lane] = v;
-    s_off[w][lane] = off;
+    const int2 vw = s_view[v];
+    const uint32_t rx = cur.r.x & 0xffffu, ry = cur.r.x >> 16, width = (cur.r.y & 0xffffu) - rx + 1u;
+    s_pair[w][lane] = make_uint4(off, vi, (uint32_t)(vw.x + (int32_t)(ry * (uint32_t)vw.y + rx)),
+                                 width | ((uint32_t)vw.y << 16));
     uint32_t stop = cur.end;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) stop = max(stop, (uint32_t)__shfl_xor((int)stop, d, 64));
@@ -641,23 +644,26 @@ __device__ __forceinline__ void emit_walk(WalkLds& L, const uint32_t* sorted_vis
     __builtin_amdgcn_sched_barrier(0);
     nxt = load_pair(koff, sorted_vis, sorted_rect, g + NW * 64u + (uint32_t)lane, nvis, all_keys);
     __builtin_amdgcn_wave_barrier();
-    const uint32_t start = max(s_off[w][0], (uint32_t)S0);
-    // the last pair of the group that began at or before `start`
-    int carry = (int)__popcll(__ballot(valid && off <= start)) - 1;
+    const uint32_t start = max(s_pair[w][0].x, (uint32_t)S0);
+    // the last pair of the group that began before `start` (-1: none)
+    int carry = (int)__popcll(__ballot(valid && off < start)) - 1;
     for (uint32_t S = start; S < stop; S += 64) {
-      s_mark[w][lane] = -1;
+      s_mark[w][lane] = 0u;
       __builtin_amdgcn_wave_barrier();
-      if (valid && off >= S && off - S < 64u) s_mark[w][off - S] = lane;
+      if (valid && off >= S && off - S < 64u) s_mark[w][off - S] = 1u;
       __builtin_amdgcn_wave_barrier();
-      const int own = wave_incl_max(max(s_mark[w][lane], carry));
-      carry = __builtin_amdgcn_readlane(own, 63);
+      // every pair has a key, so starts are distinct: the pairs that start at
+      // or before a slot of this round are counted by its lane's bit prefix
+      const uint32_t mark = s_mark[w][lane];
+      const uint64_t starts = __ballot(mark != 0u);
+      const int own = carry + (int)(__builtin_amdgcn_mbcnt_hi((uint32_t)(starts >> 32),
+                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)starts, mark)));
+      carry += (int)__popcll(starts);
       __builtin_amdgcn_wave_barrier();
       const uint32_t slot = S + (uint32_t)lane;
       if (slot < stop) {
-        const uint2 rr = s_rect[w][own];
-        const uint32_t rx = rr.x & 0xffffu, ry = rr.x >> 16;
-        const uint32_t m = slot - s_off[w][own];
-        const uint32_t width = (rr.y & 0xffffu) - rx + 1u;
+        const uint4 pr = s_pair[w][own];
+        const uint32_t m = slot - pr.x, width = pr.w & 0xffffu;
         uint32_t q = (uint32_t)((float)m * __builtin_amdgcn_rcpf((float)width));
         int32_t rem = (int32_t)(m - q * width);
         if (rem < 0) {
@@ -667,34 +673,36 @@ __device__ __forceinline__ void emit_walk(WalkLds& L, const uint32_t* sorted_vis
           q += 1u;
           rem -= (int32_t)width;
         }
-        const uint32_t ty = ry + q, tx = rx + (uint32_t)rem;
-        const int2 vw = s_view[s_v[w][own]];
-        const uint32_t key = (uint32_t)(vw.x + (int32_t)(ty * (uint32_t)vw.y + tx));
-        emit(slot, key, s_vi[w][own]);
+        emit(slot, pr.z + q * (pr.w >> 16) + (uint32_t)rem, pr.y);
       }
     }
     __builtin_amdgcn_wave_barrier();
   }
 }
 
-// Digit counts of the tile sort's first pass (key bits dmask0, a power of
-// two minus one) for every chunk, in the layout k_radix_hist writes
-// (hist[d * nblocks + c]), without producing the keys: the keys a pair has
-// in one tile row of its rectangle are consecutive integers, so the row adds
-// one to every digit len / (dmask0 + 1) times and to a cyclic range of
-// len % (dmask0 + 1) digits once.  Each lane takes one pair of the chunk
-// (clipped to the chunk's slots) row by row; the ranges go into a
+// Digit counts of the tile sort's first pass for every chunk, in the layout
+// k_radix_hist writes, without producing the keys: the keys a pair has in one
+// tile row of its rectangle are consecutive integers.  Each lane takes one
+// pair of the chunk (clipped to the chunk's slots) row by row.
+// kMsd (digits key >> low_bits): a row's keys lie in one digit, or in a few
+// consecutive ones, each counted with one LDS add.  Otherwise (digits key &
+// dmask0): a row adds one to every digit len / (dmask0 + 1) times and to a
+// cyclic range of len % (dmask0 + 1) digits once; the ranges go into a
 // difference array, whose prefix sums are the counts.
-__global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, const uint32_t* koff,
-                                                  const uint32_t* firsts, const uint32_t* nvis_p,
-                                                  const uint32_t* total_keys, const uint2* sorted_rect,
-                                                  const ViewInfo* views, int32_t n_views, int64_t n_gauss,
-                                                  int32_t tile_begin, uint32_t cap, int64_t nblocks, uint32_t dmask0,
-                                                  uint32_t* hist, bool direct, Counters* ctr, uint2* ranges,
-                                                  int64_t ntiles) {
+constexpr int kCountBlock = 256;   // (more threads than a chunk's 650 pairs can feed measured slower)
+constexpr int kCountWaves = kCountBlock / 64;
+
+template <bool kMsd>
+__global__ __launch_bounds__(kCountBlock) void k_emit_count(const uint32_t* sorted_vis, const uint32_t* koff,
+                                                            const uint32_t* firsts, const uint32_t* nvis_p,
+                                                            const uint32_t* total_keys, const uint2* sorted_rect,
+                                                            const ViewInfo* views, int32_t n_views, int64_t n_gauss,
+                                                            int32_t tile_begin, uint32_t cap, int64_t nblocks,
+                                                            uint32_t dmask0, int low_bits, uint32_t* hist, bool direct,
+                                                            Counters* ctr, uint2* ranges, int64_t ntiles) {
   __shared__ int32_t s_diff[257];
   __shared__ uint32_t s_full;
-  __shared__ uint32_t s_tmp[NW];
+  __shared__ uint32_t s_tmp[kCountWaves];
   __shared__ int2 s_view[kMaxViews];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   s_diff[threadIdx.x] = 0;
@@ -702,7 +710,7 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
     s_diff[256] = 0;
     s_full = 0u;
   }
-  for (int v = threadIdx.x; v < n_views; v += B) s_view[v] = make_int2(views[v].tile_base - tile_begin, views[v].tiles_x);
+  for (int v = threadIdx.x; v < n_views; v += kCountBlock) s_view[v] = make_int2(views[v].tile_base - tile_begin, views[v].tiles_x);
   __syncthreads();
   const uint32_t all_keys = *total_keys;
   // on the side (launches of their own would cost 4 us each): the build's key
@@ -714,7 +722,8 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
       ctr->overflow_any = 1u;
     }
   }
-  for (int64_t t = (int64_t)blockIdx.x * B + threadIdx.x; t < ntiles; t += (int64_t)gridDim.x * B)
+  for (int64_t t = (int64_t)blockIdx.x * kCountBlock + threadIdx.x; t < ntiles;
+       t += (int64_t)gridDim.x * kCountBlock)
     ranges[t] = make_uint2(0u, 0u);
   const uint32_t n = min(all_keys, cap);
   const uint32_t M = dmask0 + 1u;
@@ -729,7 +738,7 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
     // before the group in hand is counted
     uint32_t g = firsts[blockIdx.x] + (uint32_t)w * 64u;
     PairIn nxt = load_pair(koff, sorted_vis, sorted_rect, g + (uint32_t)lane, nvis, all_keys);
-    for (; g < nvis; g += NW * 64u) {
+    for (; g < nvis; g += kCountWaves * 64u) {
       const PairIn cur = nxt;
       if ((uint32_t)__builtin_amdgcn_readfirstlane((int)cur.off) >= S1) break;   // the group starts past the chunk
       const bool valid = g + (uint32_t)lane < nvis;
@@ -754,13 +763,22 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
       const uint32_t q1 = (m1 - 1u) / width, c1 = (m1 - 1u) - q1 * width;
       // so the next group's loads stay in flight while this one is counted
       __builtin_amdgcn_sched_barrier(0);
-      nxt = load_pair(koff, sorted_vis, sorted_rect, g + NW * 64u + (uint32_t)lane, nvis, all_keys);
+      nxt = load_pair(koff, sorted_vis, sorted_rect, g + kCountWaves * 64u + (uint32_t)lane, nvis, all_keys);
       if (valid && lo < hi) {
         uint32_t full = 0;
         for (uint32_t q = q0; q <= q1; ++q) {
           const uint32_t cs = q == q0 ? c0 : 0u, ce = q == q1 ? c1 : width - 1u;
           const uint32_t a = (uint32_t)(vw.x + (int32_t)((ry + q) * (uint32_t)vw.y + rx + cs));
-          const uint32_t len = ce - cs + 1u;
+          uint32_t len = ce - cs + 1u;
+          if constexpr (kMsd) {
+            for (uint32_t at = a; len != 0u;) {
+              const uint32_t d = at >> low_bits, here = min(len, ((d + 1u) << low_bits) - at);
+              atomicAdd(&s_diff[d], (int32_t)here);
+              at += here;
+              len -= here;
+            }
+            continue;
+          }
           full += len >> bits0;
           const uint32_t rem = len & dmask0;
           if (rem) {
@@ -780,26 +798,51 @@ __global__ __launch_bounds__(B) void k_emit_count(const uint32_t* sorted_vis, co
   }
   __syncthreads();
   const uint32_t d = threadIdx.x;
-  const int32_t x = d < M ? s_diff[d] : 0;
-  uint32_t total;
-  const uint32_t below = block_excl_scan((uint32_t)x, s_tmp, &total);
-  hist[hist_at(d, blockIdx.x, nblocks, direct)] = d < M ? below + (uint32_t)x + s_full : 0u;
+  if constexpr (kMsd) {
+    hist[hist_at(d, blockIdx.x, nblocks, direct)] = (uint32_t)s_diff[d];
+  } else {
+    const int32_t x = d < M ? s_diff[d] : 0;
+    uint32_t total;
+    const uint32_t below = block_excl_scan<kCountWaves>((uint32_t)x, s_tmp, &total);
+    hist[hist_at(d, blockIdx.x, nblocks, direct)] = d < M ? below + (uint32_t)x + s_full : 0u;
+  }
+}
+
+// Buckets of the tile sort: the keys of one value of their high bits, adjacent
+// after the first pass.  The second pass takes each bucket's keys in chunks of
+// its own (starting at the 16-entry boundary before the bucket's first key, so
+// that their bytes can be read 8 at a time): start[b] = first key, start[256] =
+// all keys, chunk0[b] = chunks of the buckets before b, chunk0[256] = all chunks.
+struct BucketTable {
+  uint32_t start[257];
+  uint32_t chunk0[257];
+};
+
+__device__ __forceinline__ uint32_t bucket_chunks(uint32_t start, uint32_t end) {
+  return end > start ? (end - (start & ~15u) + kSortChunk - 1) / kSortChunk : 0u;
 }
 
 // The tile sort's first pass fused with the key emission: workgroup c walks
 // its chunk's slots again, places each (key, value) at its slot in LDS, and
-// then ranks and scatters them as k_radix_scatter does (digits key & dmask0,
-// hist_scanned the scanned counts of k_emit_count), so the emitted keys
-// never go through HBM in slot order.  Its LDS use is kept at 40 KB (the
-// walk's staging shares space with the ranking's counters) for four
-// workgroups per compute unit; with 48 KB and three it was no faster than
-// emitting and sorting in separate kernels.
+// then ranks and scatters them as k_radix_scatter does (digits (key >> shift)
+// & dmask0, hist the counts of k_emit_count, scanned unless direct), so the
+// emitted keys never go through HBM in slot order.  With kKeyBytes 1 or 0 the
+// digit is the key's highest bits and the pass splits the keys into buckets,
+// whose table the first workgroup writes; of each key only the bits below go
+// on (1), or, when there are none, the buckets are the tiles and their ranges
+// are written here (0).  Three workgroups of eight wavefronts fit a compute
+// unit (45 KB of LDS; the walk's staging shares space with the ranking's
+// counters).  Bound by vector instructions: 58M keys of 16 views take 287 us,
+// 350 with eight ballots a key, selects of 64-bit masks and a max-scan for the
+// owner of a slot.
+template <int kKeyBytes>
 __global__ __launch_bounds__(B) void k_emit_scatter(const uint32_t* sorted_vis, const uint32_t* koff,
                                                     const uint32_t* firsts, const uint32_t* nvis_p,
                                                     const uint32_t* total_keys, const uint2* sorted_rect,
                                                     const ViewInfo* views, int32_t n_views, int64_t n_gauss,
                                                     int32_t tile_begin, uint32_t cap, int64_t nblocks, uint32_t dmask0,
-                                                    const uint32_t* hist, bool direct, uint32_t* kout, uint32_t* vout) {
+                                                    int shift, const uint32_t* hist, bool direct, uint32_t* kout,
+                                                    uint32_t* vout, BucketTable* buckets, uint2* ranges) {
   __shared__ __align__(16) uint32_t s_kv[2 * kSortChunk];   // keys | values
   __shared__ int2 s_view[kMaxViews];
   __shared__ union {   // the walk's staging, then the ranking's counters
@@ -817,15 +860,40 @@ __global__ __launch_bounds__(B) void k_emit_scatter(const uint32_t* sorted_vis, 
   const uint32_t all_keys = *total_keys;
   const uint32_t n = min(all_keys, cap);
   const uint64_t S0 = (uint64_t)blockIdx.x * kSortChunk;
-  if (S0 >= n) return;
+  if (S0 >= n) {
+    if (kKeyBytes == 1 && blockIdx.x == 0)   // no keys at all
+      for (int q = threadIdx.x; q < 257; q += B) buckets->start[q] = buckets->chunk0[q] = 0u;
+    return;
+  }
   const uint32_t S1 = (uint32_t)min((uint64_t)n, S0 + kSortChunk);
   const uint32_t cnt = S1 - (uint32_t)S0;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int v = threadIdx.x; v < n_views; v += B) s_view[v] = make_int2(views[v].tile_base - tile_begin, views[v].tiles_x);
-  uint32_t digit_base = direct ? 0u : hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+  uint32_t digit_base = direct || threadIdx.x >= 256 ? 0u : hist[(int64_t)threadIdx.x * nblocks + blockIdx.x];
   if (direct) {   // uniform
     uint32_t all;
     digit_base = direct_digit_base(hist, (n + kSortChunk - 1) / kSortChunk, s_scan, &all);
+  }
+  if (kKeyBytes != 4 && blockIdx.x == 0) {
+    // the first chunk's digit starts are the buckets'
+    const uint32_t d = threadIdx.x;
+    if (d < 256) s_scan[NW + d] = digit_base;
+    __syncthreads();
+    const uint32_t end = d < 255 ? s_scan[NW + d + 1] : n;
+    if constexpr (kKeyBytes == 0) {
+      if (d < 256 && end > digit_base) ranges[d] = make_uint2(digit_base, end);
+    } else {
+      uint32_t all;
+      const uint32_t c0 = block_excl_scan(d < 256 ? bucket_chunks(digit_base, end) : 0u, s_scan, &all);
+      if (d < 256) {
+        buckets->start[d] = digit_base;
+        buckets->chunk0[d] = c0;
+      }
+      if (d == 0) {
+        buckets->start[256] = n;
+        buckets->chunk0[256] = all;
+      }
+    }
   }
   __syncthreads();
   emit_walk(u.walk, sorted_vis, koff, firsts, *nvis_p, all_keys, sorted_rect, s_view, (uint32_t)n_gauss, S0, S1,
@@ -846,13 +914,135 @@ __global__ __launch_bounds__(B) void k_emit_scatter(const uint32_t* sorted_vis, 
     in_mask |= in ? 1u << r : 0u;
   }
 #pragma unroll
-  for (int q = 0; q < NW; ++q) u.rank.wc[q][threadIdx.x] = 0;
+  for (int q = 0; q < NW * 256 / B; ++q) (&u.rank.wc[0][0])[q * B + threadIdx.x] = 0;
   // the ranking places keys into the same LDS space
   __syncthreads();
   uint32_t pos[kWaveRounds];
   uint32_t dst[1];
-  rank_and_write<false, true>(key, val, in_mask, digit_base, 0, dmask0, s_key, s_val, u.rank.wc, u.rank.gbase,
-                              u.rank.tmp, u.rank.taken, kout, vout, pos, dst, n);
+  rank_and_write<false, true, kKeyBytes>(key, val, in_mask, digit_base, shift, dmask0, s_key, s_val, u.rank.wc,
+                                         u.rank.gbase, u.rank.tmp, u.rank.taken, kout, vout, pos, dst, n);
+}
+
+// ---- second pass of a tile sort of 9 to 16 bits: inside the buckets ----------
+// Bound by memory: per key one byte and the value are read and the value is
+// written, and the ranges fall out of the digit starts, 15 bytes a key for the
+// whole sort with the first pass; as a second pass over whole 32-bit keys, a
+// range extraction after it, it took 32.
+struct BucketChunk {
+  uint32_t bucket, index, chunks;   // of the chunk; the chunk's index in its bucket; the bucket's chunks
+  uint32_t row0;                    // chunks of the buckets before
+  uint32_t start, end;              // the bucket's keys
+  uint32_t base;                    // first entry of the chunk, a multiple of 16 (entries before start are not its)
+};
+
+// Finds chunk blockIdx.x's bucket; false past the last chunk (uniform).
+__device__ __forceinline__ bool find_bucket(const BucketTable* t, uint32_t* s_bucket, BucketChunk& c) {
+  const uint32_t me = blockIdx.x;
+  if (me >= t->chunk0[256]) return false;
+  if (threadIdx.x < 256 && t->chunk0[threadIdx.x] <= me && me < t->chunk0[threadIdx.x + 1]) *s_bucket = threadIdx.x;
+  __syncthreads();
+  c.bucket = __builtin_amdgcn_readfirstlane(*s_bucket);
+  c.row0 = t->chunk0[c.bucket];
+  c.chunks = t->chunk0[c.bucket + 1] - c.row0;
+  c.index = me - c.row0;
+  c.start = t->start[c.bucket];
+  c.end = t->start[c.bucket + 1];
+  c.base = (c.start & ~15u) + c.index * (uint32_t)kSortChunk;
+  return true;
+}
+
+// Digit counts of a bucket's chunks: chunk by chunk (direct), else digit by
+// digit within each bucket, so that one scan over all of them gives every
+// (bucket, digit, chunk) its place.
+__global__ __launch_bounds__(B) void k_bucket_hist(const uint8_t* keys, const BucketTable* table, int low_bits,
+                                                   uint32_t* hist, bool direct, uint32_t* rows) {
+  __shared__ uint32_t h[NW][256][kHistCopies];
+  __shared__ uint32_t s_bucket;
+#pragma unroll
+  for (int q = 0; q < NW * kHistCopies * 256 / B; ++q) (&h[0][0][0])[q * B + threadIdx.x] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *rows = table->chunk0[256] << low_bits;
+  BucketChunk c;
+  if (!find_bucket(table, &s_bucket, c)) return;
+  constexpr uint32_t kPer = kSortChunk / B;
+  static_assert(kPer == 8, "one 8-byte load per thread");
+  const uint32_t at = c.base + threadIdx.x * kPer;
+  const int w = threadIdx.x >> 6, copy = threadIdx.x & (kHistCopies - 1);
+  if (at < c.end) {   // (the key buffers hold whole 8-byte words: their capacity is rounded up)
+    const uint2 x = *reinterpret_cast<const uint2*>(keys + at);
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k)
+      if (at + k >= c.start && at + k < c.end)
+        atomicAdd(&h[w][((k < 4 ? x.x : x.y) >> (8 * (k & 3))) & 255u][copy], 1u);
+  }
+  __syncthreads();
+  const uint32_t d = threadIdx.x, D = 1u << low_bits;
+  if (d >= D) return;
+  uint32_t t = 0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q)
+#pragma unroll
+    for (int k = 0; k < kHistCopies; ++k) t += h[q][d][k];
+  hist[direct ? (size_t)(c.row0 + c.index) * D + d : (size_t)c.row0 * D + (size_t)d * c.chunks + c.index] = t;
+}
+
+__global__ __launch_bounds__(B) void k_bucket_scatter(const uint8_t* keys, const uint32_t* vin, const BucketTable* table,
+                                                      int low_bits, const uint32_t* hist, bool direct, uint32_t* vout,
+                                                      uint2* ranges) {
+  __shared__ __align__(16) uint32_t s_kv[2 * kSortChunk];
+  __shared__ uint32_t s_wc[NW][256];
+  __shared__ uint32_t s_gbase[256];
+  __shared__ uint32_t s_tmp[NW];
+  __shared__ uint32_t s_taken;
+  __shared__ uint32_t s_bucket;
+  BucketChunk c;
+  if (!find_bucket(table, &s_bucket, c)) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t d = threadIdx.x, D = 1u << low_bits;
+#pragma unroll
+  for (int q = 0; q < NW * 256 / B; ++q) (&s_wc[0][0])[q * B + threadIdx.x] = 0;
+  uint32_t digit_base = 0;
+  if (!direct && d < D) digit_base = hist[(size_t)c.row0 * D + (size_t)d * c.chunks + c.index];
+  uint32_t key[kWaveRounds], val[kWaveRounds];
+  uint32_t in_mask = 0;
+  const uint32_t at0 = c.base + (uint32_t)w * kWaveKeys + (uint32_t)lane;
+#pragma unroll
+  for (int r = 0; r < kWaveRounds; ++r) {
+    // (keys and values outside the bucket are read, where the buffers hold
+    // them, and not taken)
+    const uint32_t at = min(at0 + (uint32_t)r * 64u, c.end - 1u);
+    key[r] = __builtin_nontemporal_load(keys + at);
+    val[r] = __builtin_nontemporal_load(vin + at);
+  }
+#pragma unroll
+  for (int r = 0; r < kWaveRounds; ++r) {
+    const uint32_t at = at0 + (uint32_t)r * 64u;
+    in_mask |= at >= c.start && at < c.end ? 1u << r : 0u;
+  }
+  if (direct) {   // uniform
+    uint32_t before = 0, total = 0, all;
+    if (d < D) {
+#pragma unroll 8
+      for (uint32_t k = 0; k < c.chunks; ++k) {
+        const uint32_t x = hist[(size_t)(c.row0 + k) * D + d];
+        before += k < c.index ? x : 0u;
+        total += x;
+      }
+    }
+    digit_base = c.start + block_excl_scan(total, s_tmp, &all) + before;
+  }
+  if (c.index == 0) {   // uniform: the first chunk's digit starts are the tiles'
+    if (d < D) s_gbase[d] = digit_base;
+    __syncthreads();
+    if (d < D) {
+      const uint32_t end = d + 1u < D ? s_gbase[d + 1] : c.end;
+      if (end > digit_base) ranges[(c.bucket << low_bits) + d] = make_uint2(digit_base, end);
+    }
+  }
+  __syncthreads();
+  uint32_t pos[kWaveRounds];
+  uint32_t dst[1];
+  rank_and_write<false, true, 0>(key, val, in_mask, digit_base, 0, D - 1u, s_kv, s_kv + kSortChunk, s_wc, s_gbase, s_tmp,
+                                 s_taken, nullptr, vout, pos, dst, c.end);
 }
 
 // Per-tile [start, end) of the sorted keys; thread q looks at keys 4q..4q+3
@@ -1074,10 +1264,13 @@ __global__ __launch_bounds__(B) void k_small_fill(const ViewInfo* views, const i
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   uint32_t before = 0;
   for (uint32_t q = threadIdx.x; q < blockIdx.x; q += B) {
-    const uint4 c = reinterpret_cast<const uint4*>(tile_count)[q];
-    before += (c.x + c.y) + (c.z + c.w);
+#pragma unroll
+    for (int k = 0; k < NW / 4; ++k) {
+      const uint4 c = reinterpret_cast<const uint4*>(tile_count)[q * (NW / 4) + k];
+      before += (c.x + c.y) + (c.z + c.w);
+    }
   }
-  static_assert(NW == 4, "a tile's counts are read as one uint4");
+  static_assert(NW % 4 == 0, "a tile's counts are read 16 bytes at a time");
   uint32_t base;
   block_excl_scan(before, s_tmp, &base);
   uint32_t cnt[NW], at = base, all = 0;
@@ -1246,7 +1439,7 @@ static hipError_t order_tiles(const Plan& pl, void* ws, int32_t tile_begin, int6
 static bool small_lists(const Plan& pl, int nv, int64_t ntiles) {
   const int64_t n = pl.n;
   return n <= kSmallN && n * n * nv <= kSmallCompares && n * ntiles <= kSmallCovers &&
-         16 * ntiles <= (int64_t)(pl.ws.vals_a - pl.ws.vrect_b);   // the tile counts' scratch
+         4 * NW * ntiles <= (int64_t)(pl.ws.vals_a - pl.ws.vrect_b);   // the tile counts' scratch
 }
 
 hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream_t st) {
@@ -1307,37 +1500,64 @@ hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream
   if (e != hipSuccess) return e;
   // 4. digit counts of the tile sort's first pass over the (tile, value)
   // pairs in depth order, one sort chunk per workgroup, and their scan
-  // tile bits of the call, split into passes of 8 bits with the remainder
-  // taken first: fewer digits in the first pass
+  // tile bits of the call: up to 16 are sorted from the highest bits down, in
+  // one pass or two of half the bits each; more, from the lowest up in passes
+  // of 8 with the remainder first
   int bits = 0;
   while ((1ll << bits) < ntiles) ++bits;
   if (bits == 0) bits = 1;
-  const int first_bits = bits - 8 * ((bits - 1) / 8);
+  const bool msd = bits <= 16;
+  const int low_bits = !msd || bits <= 8 ? 0 : bits / 2;
+  const int first_bits = msd ? bits - low_bits : bits - 8 * ((bits - 1) / 8);
   uint32_t* hist = seg<uint32_t>(ws, pl.ws.hist);
   const uint32_t dmask0 = (1u << first_bits) - 1u;
   const bool direct = key_chunks <= kDirectChunks;
-  hipLaunchKernelGGL(k_emit_count, dim3((unsigned)key_chunks), dim3(B), 0, st, sorted_vis, koff, firsts, &ctr->nvis,
-                     &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N, tile_begin, cap, key_chunks, dmask0, hist, direct, ctr,
-                     ranges + tile_begin, ntiles);
+  hipLaunchKernelGGL(msd ? k_emit_count<true> : k_emit_count<false>, dim3((unsigned)key_chunks), dim3(kCountBlock), 0,
+                     st, sorted_vis, koff, firsts, &ctr->nvis, &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N,
+                     tile_begin, cap, key_chunks, dmask0, low_bits, hist, direct, ctr, ranges + tile_begin, ntiles);
   if (!direct) {
     e = scan_src(ScanSrc{hist, nullptr, 0}, hist, 256 * key_chunks, nullptr, partial, pl.ws.partial_len, nullptr, st);
     if (e != hipSuccess) return e;
   }
   // 5. stable sort by tile (relative to the first tile of the call): its
-  // first pass fused with the emission, into the second buffers
-  hipLaunchKernelGGL(k_emit_scatter, dim3((unsigned)key_chunks), dim3(B), 0, st, sorted_vis, koff, firsts, &ctr->nvis,
-                     &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N, tile_begin, cap, key_chunks, dmask0, hist, direct,
-                     keys_b, vals_b);
-  e = radix_sort(pl, ws, keys_a, vals_a, keys_b, vals_b, nullptr, nullptr, pl.cap, &ctr->keys, bits, &in_b, st, nullptr,
-                 true, first_bits);
-  if (e != hipSuccess) return e;
-  // 6. ranges (empty ones were written with the digit counts)
-  const uint32_t* sk = in_b ? keys_b : keys_a;
-  // one quad of keys per thread (the loop in the kernel covers any size):
-  // every wavefront's loads are in flight at once instead of one quad after
-  // another per thread
-  const int64_t rblocks = cdiv(cdiv(pl.cap, 4), 256) < 0x7fffffffll ? cdiv(cdiv(pl.cap, 4), 256) : 0x7fffffffll;
-  hipLaunchKernelGGL(k_ranges, dim3((unsigned)rblocks), dim3(256), 0, st, sk, &ctr->keys, cap, tile_begin, ranges);
+  // first pass fused with the emission, into the second buffers (empty tiles'
+  // ranges were written with the digit counts)
+  BucketTable* buckets = seg<BucketTable>(ws, pl.ws.buckets);
+  auto emit = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)key_chunks), dim3(B), 0, st, sorted_vis, koff, firsts, &ctr->nvis,
+                       &ctr->keys, sorted_rect, pl.d_views, pl.n_views, N, tile_begin, cap, key_chunks, dmask0,
+                       low_bits, hist, direct, keys_b, vals_b, buckets, ranges + tile_begin);
+  };
+  if (msd && low_bits == 0) {
+    emit(k_emit_scatter<0>);
+  } else if (msd) {
+    emit(k_emit_scatter<1>);
+    const uint8_t* low = reinterpret_cast<const uint8_t*>(keys_b);
+    // every bucket's last chunk may be a partial one
+    const int64_t chunks = key_chunks + cdiv(ntiles, 1ll << low_bits);
+    // (in a workspace word that nothing else holds now)
+    uint32_t* rows = firsts;
+    hipLaunchKernelGGL(k_bucket_hist, dim3((unsigned)chunks), dim3(B), 0, st, low, buckets, low_bits, hist, direct, rows);
+    if (!direct) {
+      e = scan_src(ScanSrc{hist, nullptr, 0}, hist, chunks << low_bits, rows, partial, pl.ws.partial_len, nullptr, st);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_bucket_scatter, dim3((unsigned)chunks), dim3(B), 0, st, low, vals_b, buckets, low_bits, hist,
+                       direct, vals_a, ranges + tile_begin);
+  } else {
+    emit(k_emit_scatter<4>);
+    e = radix_sort(pl, ws, keys_a, vals_a, keys_b, vals_b, nullptr, nullptr, pl.cap, &ctr->keys, bits, &in_b, st,
+                   nullptr, true, first_bits);
+    if (e != hipSuccess) return e;
+    // 6. ranges
+    const uint32_t* sk = in_b ? keys_b : keys_a;
+    // one quad of keys per thread (the loop in the kernel covers any size):
+    // every wavefront's loads are in flight at once instead of one quad after
+    // another per thread
+    const int64_t rblocks = cdiv(cdiv(pl.cap, 4), 256) < 0x7fffffffll ? cdiv(cdiv(pl.cap, 4), 256) : 0x7fffffffll;
+    hipLaunchKernelGGL(k_ranges, dim3((unsigned)rblocks), dim3(256), 0, st, sk, &ctr->keys, cap, tile_begin, ranges);
+  }
+  // 7. longest-first order of the call's tiles for the persistent compositing kernels
   return order_tiles(pl, ws, tile_begin, ntiles, st);
 }
 

@@ -137,6 +137,27 @@ def test_tile_lists_either_side_of_the_small_model_bounds(oracle, n, sizes, tile
     assert np.array_equal(seg_np(r, "ranges", np.uint32).reshape(-1, 2), ranges_o)
 
 
+@pytest.mark.parametrize("cap", [1 << 20, 1 << 22])   # histograms read as they are / scanned
+@pytest.mark.parametrize("n,sizes,tile", [
+    (16385, ((64, 48),), (8, 8)),              # 6 tile bits: the first pass's buckets are the tiles
+    (16385, ((128, 128),), (8, 8)),            # 8 bits, every one of 256 tiles
+    (16400, ((136, 128),), (8, 8)),            # 9 bits: buckets of 16 tiles, the last one ragged
+    (2100, ((1280, 720), (1000, 64)), (8, 8)),   # 14 bits, long lists: buckets of many chunks
+    (600, ((1280, 720),) * 5, (8, 8))])        # 17 bits: lowest digits first
+def test_tile_lists_by_tile_bits_bit_exact(oracle, n, sizes, tile, cap):
+    w = small(seed=151, n=n, sizes=sizes)
+    w.scene.log_scale[:, :3] = -0.7            # pairs that straddle sort chunks
+    r = renderer_for(w, tile=tile, cap=cap)
+    P = DeviceParams.from_scene(w.scene)
+    for _ in range(2):                         # the second build finds the first one's buckets and counts
+        r.forward(P)
+        c = r.counters()
+        vals_o, ranges_o = oracle.tile_lists(w.scene, w.cams, *tile)
+        assert c.overflow == 0 and c.keys == len(vals_o) <= cap
+        assert np.array_equal(seg_np(r, "sorted_values", np.uint32)[:c.keys], vals_o)
+        assert np.array_equal(seg_np(r, "ranges", np.uint32).reshape(-1, 2), ranges_o)
+
+
 def test_small_model_overflow_is_reported():
     w = small(seed=102)
     r = renderer_for(w, cap=100)
@@ -145,6 +166,30 @@ def test_small_model_overflow_is_reported():
     r.ctx.build_tile_lists(0, r.n_views, r.ws)
     c = r.counters()
     assert c.overflow == 1 and c.keys > 100 and r.capacity_exceeded
+
+
+@pytest.mark.parametrize("n,cap", [(1500, 1), (16385, 100), (16385, 5000)])   # compared, sorted
+def test_overflow_is_reported_and_stays_within_the_capacity(n, cap):
+    w = small(seed=102, n=n)
+    r = renderer_for(w, cap=cap)
+    P = DeviceParams.from_scene(w.scene)
+    r.ctx.project(P, r.dev_cams, 0, r.n_views, r.ws)
+    r.ctx.build_tile_lists(0, r.n_views, r.ws)
+    c = r.counters()
+    assert c.overflow == 1 and c.keys > cap and c.key_capacity == cap and r.capacity_exceeded
+    assert seg_np(r, "ranges", np.uint32).max() <= cap
+
+
+def test_no_visible_pair_gives_empty_lists():
+    for n in (1500, 16385):                    # compared, sorted
+        w = small(seed=102, n=n)
+        w.scene.mean[...] = np.nan
+        r = renderer_for(w, cap=1 << 16)
+        P = DeviceParams.from_scene(w.scene)
+        r.forward(P)
+        c = r.counters()
+        assert c.keys == 0 and c.visible == 0 and c.overflow == 0
+        assert not seg_np(r, "ranges", np.uint32).any() and float(r.T.min()) == 1.0
 
 
 @pytest.mark.parametrize("bg", [(0.0, 0.0, 0.0), (0.3, 0.5, 0.1)])
