@@ -256,18 +256,25 @@ struct ProjArgs {
   int tile_sw, tile_sh;      // log2 of the tile width and height
   uint32_t* depth;
   uint32_t* count;
-  ushort4* rect;
+  uint2* rect;               // (x0 | y0 << 16, x1 | y1 << 16)
   float4* rec;
+  bool stream_rec;           // the call's records exceed the last-level cache
   uint64_t* vmask;           // per Gaussian: the views of this call that see it
   const uint32_t* cell_of;   // preculling (null = off)
   const uint8_t* cell_mask;
   int32_t cell_row;
 };
 
+// Visible lanes from which a wavefront stores the entries of all of its lanes
+// (a wavefront's 256 bytes of a 4-byte array are two lines or more: with a
+// dozen lanes written none of them is left untouched, and few are whole).
+constexpr int kWholeLanes = 12;
+
 constexpr int kViewWaves = 1;   // (the per-Gaussian view mask assumes a single wavefront per Gaussian)
 static_assert(kViewWaves == 1, "one wavefront writes a Gaussian's view mask");
 
-template <int DEG>
+// kCells: with preculling.
+template <int DEG, bool kCells>
 __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
   const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
   // uniform, so that the per-view camera is read with scalar loads
@@ -275,38 +282,54 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
   const int64_t n = a.p.n;
   if (i >= n || wave >= a.nv) return;
   constexpr int nk = (DEG + 1) * (DEG + 1);
-  const uint32_t cell = a.cell_mask ? a.cell_of[i] : 0u;
-  if (a.cell_mask) {
+  const uint32_t cell = kCells ? a.cell_of[i] : 0u;
+  bool any = true;
+  if constexpr (kCells) {
     // a Gaussian whose cell no view of the call can see is culled everywhere
     // without touching its parameters
-    bool any = false;
+    any = false;
     for (int v = a.v0 + wave; v < a.v0 + a.nv; v += kViewWaves) any |= a.cell_mask[(int64_t)v * a.cell_row + cell] != 0;
-    if (!any) {
+    // (the wavefront stays whole: its lanes store each other's records)
+    if (__ballot(any) == 0ull) {
       for (int v = a.v0 + wave; v < a.v0 + a.nv; v += kViewWaves) a.count[(int64_t)v * n + i] = 0u;
       a.vmask[i] = 0ull;
       return;
     }
   }
-  // SH coefficients parked in this wavefront's own LDS columns (each lane
-  // reads back only what it wrote, so no barrier is needed)
-  __shared__ float s_sh[kViewWaves][3 * nk][64];
+  // SH coefficients: the first kShRegs in registers, the rest parked in this
+  // wavefront's own LDS columns (each lane reads back only what it wrote, so
+  // no barrier is needed); with all 48 there and the records' staging beside
+  // them, a compute unit would hold 10 wavefronts instead of 13
+  constexpr int kShRegs = 3 * nk < 11 ? 3 * nk : 11;
+  constexpr int kShLds = 3 * nk - kShRegs;
+  __shared__ float s_sh[kViewWaves][kShLds ? kShLds : 1][64];
+  __shared__ float4 s_rec[kViewWaves][3 * 64];
   const int lane = threadIdx.x & 63;
   bool sh_ok = true;
-#pragma unroll
-  for (int k = 0; k < 3 * nk; ++k) {
-    const float c = __builtin_nontemporal_load(a.p.sh + (int64_t)k * n + i);
-    sh_ok &= isfinite(c);
-    s_sh[wave][k][lane] = c;
-  }
+  float sh_reg[kShRegs];
   Gauss g;
-  load_gauss(a.p, i, g, sh_ok);
+  g.ok = false;
+  if (any) {
+#pragma unroll
+    for (int k = 0; k < 3 * nk; ++k) {
+      const float c = __builtin_nontemporal_load(a.p.sh + (int64_t)k * n + i);
+      sh_ok &= isfinite(c);
+      if (k < kShRegs) sh_reg[k] = c;
+      else s_sh[wave][k - kShRegs][lane] = c;
+    }
+    load_gauss(a.p, i, g, sh_ok);
+  }
   uint64_t vm = 0ull;
+  const int lanes = (int)(n - (i - lane) < 64 ? n - (i - lane) : 64);   // of this wavefront that hold a Gaussian
 #pragma unroll 1
   for (int v = a.v0 + wave; v < a.v0 + a.nv; v += kViewWaves) {
     const int64_t o = (int64_t)v * n + i;
     const gs_camera cam = read_camera(a.cams, v);
     uint32_t cnt = 0;
-    if (g.ok && (!a.cell_mask || a.cell_mask[(int64_t)v * a.cell_row + cell])) {
+    uint2 rect = make_uint2(0u, 0u);
+    uint32_t depth = 0;
+    float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0, r2 = r0;
+    if (g.ok && (!kCells || a.cell_mask[(int64_t)v * a.cell_row + cell])) {
       const float z32 = depth_key(cam.R[6], cam.R[7], cam.R[8], cam.t[2], g.mu[0], g.mu[1], g.mu[2]);
       ViewGeom vg;
       if (z32 >= kNear && view_geom(g, read_view_d(a.vd, v), vg)) {
@@ -321,8 +344,8 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
           const int tx0 = (int)lx >> a.tile_sw, tx1 = (int)ux >> a.tile_sw;
           const int ty0 = (int)ly >> a.tile_sh, ty1 = (int)uy >> a.tile_sh;
           cnt = (uint32_t)((tx1 - tx0 + 1) * (ty1 - ty0 + 1));
-          a.rect[o] = make_ushort4((unsigned short)tx0, (unsigned short)ty0, (unsigned short)tx1, (unsigned short)ty1);
-          a.depth[o] = __float_as_uint(z32);
+          rect = make_uint2((uint32_t)tx0 | ((uint32_t)ty0 << 16), (uint32_t)tx1 | ((uint32_t)ty1 << 16));
+          depth = __float_as_uint(z32);
           // splat record
           const float uh = (float)vg.u, wh = (float)vg.w;
           const float ul = (float)(vg.u - (double)uh), wl = (float)(vg.w - (double)wh);
@@ -339,14 +362,53 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
           for (int ch = 0; ch < 3; ++ch) {
             float s = 0.5f;
 #pragma unroll
-            for (int k = 0; k < nk; ++k) s = fmaf(s_sh[wave][k * 3 + ch][lane], Y[k], s);
+            for (int k = 0; k < nk; ++k) {
+              const int c = k * 3 + ch;
+              s = fmaf(c < kShRegs ? sh_reg[c] : s_sh[wave][c - kShRegs][lane], Y[k], s);
+            }
             col[ch] = fmaxf(s, 0.f);
           }
-          a.rec[o * 3 + 0] = make_float4(uh, wh, ul, wl);
-          a.rec[o * 3 + 1] = make_float4(qa, qr, qs, g.o);
-          a.rec[o * 3 + 2] = make_float4(col[0], col[1], col[2], 0.f);
+          r0 = make_float4(uh, wh, ul, wl);
+          r1 = make_float4(qa, qr, qs, g.o);
+          r2 = make_float4(col[0], col[1], col[2], 0.f);
         }
       }
+    }
+    // Memory takes a partly written line at a fraction of its rate: storing
+    // only the visible lanes' entries, 60% of them, took 265 of this kernel's
+    // 446 us at 1M Gaussians and 16 views.  A wavefront with several visible
+    // lanes stores every lane's (the others' are never read), the 48-byte
+    // records through LDS so that each store covers whole lines, past the
+    // caches when all of them exceed the last one: 252 us.
+    const uint64_t seen = __ballot(cnt != 0u);
+    const bool whole = __popcll(seen) >= kWholeLanes;   // uniform
+    if (whole || cnt != 0u) {
+      a.rect[o] = rect;
+      a.depth[o] = depth;
+    }
+    if (whole) {
+      s_rec[wave][lane * 3 + 0] = r0;
+      s_rec[wave][lane * 3 + 1] = r1;
+      s_rec[wave][lane * 3 + 2] = r2;
+      __builtin_amdgcn_wave_barrier();
+      // the wavefront's records in pieces of 16 bytes (lanes past the last
+      // Gaussian have left: the lanes here store all pieces there are)
+      typedef float F4 __attribute__((ext_vector_type(4)));
+      const F4* src = reinterpret_cast<const F4*>(&s_rec[wave][0]);
+      F4* dst = reinterpret_cast<F4*>(a.rec + (o - lane) * 3);
+      if (a.stream_rec) {   // uniform
+#pragma unroll
+        for (int q = 0; q < 3; ++q) __builtin_nontemporal_store(src[q * lanes + lane], dst + q * lanes + lane);
+        asm volatile("");   // (the two forms would be merged into ordinary stores)
+      } else {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) dst[q * lanes + lane] = src[q * lanes + lane];
+      }
+      __builtin_amdgcn_wave_barrier();
+    } else if (cnt != 0u) {
+      a.rec[o * 3 + 0] = r0;
+      a.rec[o * 3 + 1] = r1;
+      a.rec[o * 3 + 2] = r2;
     }
     a.count[o] = cnt;
     if (cnt != 0u) vm |= a.nv <= 64 ? 1ull << (v - a.v0) : ~0ull;
@@ -621,8 +683,9 @@ hipError_t launch_project(const Plan& pl, const ParamPtrs& p, const gs_camera* c
   a.tile_sh = __builtin_ctz((unsigned)pl.tile_h);
   a.depth = seg<uint32_t>(ws, pl.ws.depth);
   a.count = seg<uint32_t>(ws, pl.ws.count);
-  a.rect = seg<ushort4>(ws, pl.ws.rect);
+  a.rect = seg<uint2>(ws, pl.ws.rect);
   a.rec = seg<float4>(ws, pl.ws.rec);
+  a.stream_rec = (int64_t)nv * p.n * (int64_t)(sizeof(float) * kRecFloats) > (256ll << 20);
   a.vmask = seg<uint64_t>(ws, pl.ws.vmask);
   a.cell_of = pl.cell_of;
   a.cell_mask = pl.cell_mask;
@@ -635,11 +698,14 @@ hipError_t launch_project(const Plan& pl, const ParamPtrs& p, const gs_camera* c
   hipLaunchKernelGGL(k_view_consts, dim3(1), dim3(kMaxViews), 0, st, cams, v0, nv, seg<ViewD>(ws, pl.ws.vconst),
                      v0 == 0 ? &seg<Counters>(ws, pl.ws.counters)->overflow : nullptr);
   const dim3 block(64 * kViewWaves);
+  auto launch = [&](auto plain, auto cells) {
+    hipLaunchKernelGGL(a.cell_mask ? cells : plain, dim3(blocks), block, 0, st, a);
+  };
   switch (p.deg) {
-    case 0: hipLaunchKernelGGL(k_project<0>, dim3(blocks), block, 0, st, a); break;
-    case 1: hipLaunchKernelGGL(k_project<1>, dim3(blocks), block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL(k_project<2>, dim3(blocks), block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL(k_project<3>, dim3(blocks), block, 0, st, a); break;
+    case 0: launch(k_project<0, false>, k_project<0, true>); break;
+    case 1: launch(k_project<1, false>, k_project<1, true>); break;
+    case 2: launch(k_project<2, false>, k_project<2, true>); break;
+    case 3: launch(k_project<3, false>, k_project<3, true>); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

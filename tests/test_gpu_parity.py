@@ -192,6 +192,32 @@ def test_no_visible_pair_gives_empty_lists():
         assert not seg_np(r, "ranges", np.uint32).any() and float(r.T.min()) == 1.0
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 130])
+@pytest.mark.parametrize("keep", [1, 11, 12, 64])
+@pytest.mark.parametrize("deg", [0, 1, 2, 3])
+def test_records_around_the_whole_line_rule(n, keep, deg):
+    """Wavefronts with fewer and more visible lanes than store their records as
+    whole lines, and a last one that is not full: the records of the visible
+    pairs are those of a model in which only they exist."""
+    w = small(seed=160 + deg, n=n, sizes=((64, 48),) * 2, deg=deg)
+    sc = w.scene
+    P = DeviceParams.from_scene(sc)
+    r = renderer_for(w, cap=1 << 16)
+    r.forward(P)
+    want = seg_np(r, "record", np.float32).reshape(2, n, 12).copy()
+    rect, depth = seg_np(r, "rect", np.uint16).reshape(2, n, 4).copy(), seg_np(r, "depth", np.uint32).reshape(2, n).copy()
+    seen = seg_np(r, "count", np.uint32).reshape(2, n) > 0
+    drop = np.arange(n) % 64 >= keep           # leave `keep` lanes of each wavefront
+    sc.mean[:, drop] = np.nan
+    r2 = renderer_for(w, cap=1 << 16)
+    r2.forward(DeviceParams.from_scene(sc))
+    left = seg_np(r2, "count", np.uint32).reshape(2, n) > 0
+    assert np.array_equal(left, seen & ~drop)
+    assert np.array_equal(seg_np(r2, "record", np.float32).reshape(2, n, 12)[left], want[left])
+    assert np.array_equal(seg_np(r2, "rect", np.uint16).reshape(2, n, 4)[left], rect[left])
+    assert np.array_equal(seg_np(r2, "depth", np.uint32).reshape(2, n)[left], depth[left])
+
+
 @pytest.mark.parametrize("bg", [(0.0, 0.0, 0.0), (0.3, 0.5, 0.1)])
 def test_composite_matches_oracle(oracle, bg):
     w = small(seed=103)
