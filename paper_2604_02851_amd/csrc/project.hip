@@ -266,8 +266,9 @@ struct ProjArgs {
 };
 
 // Visible lanes from which a wavefront stores the entries of all of its lanes
-// (a wavefront's 256 bytes of a 4-byte array are two lines or more: with a
-// dozen lanes written none of them is left untouched, and few are whole).
+// (a wavefront's 256 bytes of a 4-byte array are two lines or more). What
+// counts is that wavefronts in full view write whole lines: 1, 4 and 12 measure
+// the same, with 12 a nearly empty wavefront writes only its own entries.
 constexpr int kWholeLanes = 12;
 
 constexpr int kViewWaves = 1;   // (the per-Gaussian view mask assumes a single wavefront per Gaussian)
