@@ -229,15 +229,10 @@ hipError_t launch_sort_cells(const Plan& pl, const gs_params& p, const gs_params
   hipError_t e = launch_sort_pairs(pl, ws, ka, va, kb, vb, n, bits, &in_b, st);
   if (e != hipSuccess) return e;
   const uint32_t* from = in_b ? vb : va;   // from[k] = old position of the Gaussian that lands at k
-  // scratch: the larger of two runs of segments that hold nothing across a
-  // regrouping, the projection's pair arrays (at least 16 words per Gaussian)
-  // and the key buffers
-  uint32_t* scratch = seg<uint32_t>(ws, pl.ws.depth);
-  int64_t scratch_words = (int64_t)(pl.ws.g2 - pl.ws.depth) / 4;
-  if ((int64_t)(pl.ws.hist - pl.ws.keys_a) / 4 > scratch_words) {
-    scratch = seg<uint32_t>(ws, pl.ws.keys_a);
-    scratch_words = (int64_t)(pl.ws.hist - pl.ws.keys_a) / 4;
-  }
+  // scratch: the splat records (at least 12 words per Gaussian), which the next
+  // projection writes anew; the tile lists and what indexes into them stay
+  uint32_t* scratch = seg<uint32_t>(ws, pl.ws.rec);
+  const int64_t scratch_words = (int64_t)(pl.ws.g2 - pl.ws.rec) / 4;
   RowBatch batch;
   batch.count = 0;
   int64_t batch_len = 0;
