@@ -159,7 +159,7 @@ struct RowBatch {
 // rows as it holds, in two launches per batch: k_gather_rows writes
 // scratch[r][k] = row[r][from[k]], k_copy_back_rows returns the rows.  Bound
 // by launches when done row by row (358 launches of about 3 us for a 500k
-// model with moments, 1.23 ms a regrouping); in batches (0.34 ms) it is bound
+// model with moments, 1.23 ms a regrouping); in batches (0.42 ms) it is bound
 // by its four accesses per element.  A thread takes four consecutive positions of kGatherRows
 // rows: the permutation is read once for them, their 16 loads (scattered, but
 // near each other where the model was already grouped) are in flight
