@@ -17,6 +17,7 @@
 // visibility source (the engine's depth test in the paper) pass their own
 // per-view cell mask instead.
 #include "internal.h"
+#include "row_batch.h"
 
 namespace gs {
 namespace {
@@ -148,13 +149,6 @@ __global__ void k_cell_keys(const uint32_t* cell_of, int64_t n, int64_t n_active
   val[i] = (uint32_t)i;
 }
 
-// Rows of one permutation batch, all of the same length.
-constexpr int kPermRows = 64;
-struct RowBatch {
-  uint32_t* row[kPermRows];
-  int32_t count;
-};
-
 // The permutation moves whole batches of rows through the workspace, as many
 // rows as it holds, in two launches per batch: k_gather_rows writes
 // scratch[r][k] = row[r][from[k]], k_copy_back_rows returns the rows.  Bound
@@ -233,43 +227,29 @@ hipError_t launch_sort_cells(const Plan& pl, const gs_params& p, const gs_params
   // projection writes anew; the tile lists and what indexes into them stay
   uint32_t* scratch = seg<uint32_t>(ws, pl.ws.rec);
   const int64_t scratch_words = (int64_t)(pl.ws.g2 - pl.ws.rec) / 4;
-  RowBatch batch;
-  batch.count = 0;
-  int64_t batch_len = 0;
-  auto flush = [&]() {
-    if (batch.count == 0 || batch_len == 0) return;
-    const int64_t stride = (batch_len + 3) / 4 * 4;
-    const unsigned g = (unsigned)((batch_len + 1023) / 1024);
+  RowBatcher rows(scratch_words, [&](const RowBatch& batch, int64_t len) {
+    const int64_t stride = row_stride(len);
+    const unsigned g = (unsigned)((len + 1023) / 1024);
     hipLaunchKernelGGL(k_gather_rows, dim3(g, (unsigned)((batch.count + kGatherRows - 1) / kGatherRows)), dim3(256), 0,
-                       st, batch, from, batch_len, stride, scratch);
-    hipLaunchKernelGGL(k_copy_back_rows, dim3(g, (unsigned)batch.count), dim3(256), 0, st, batch, batch_len, stride,
-                       scratch);
-    batch.count = 0;
-  };
-  auto permute = [&](uint32_t* row, int64_t len) {
-    if (len != batch_len) {
-      flush();
-      batch_len = len;
-    }
-    batch.row[batch.count++] = row;
-    if (batch.count == kPermRows || (int64_t)(batch.count + 1) * ((len + 3) / 4 * 4) > scratch_words) flush();
-  };
+                       st, batch, from, len, stride, scratch);
+    hipLaunchKernelGGL(k_copy_back_rows, dim3(g, (unsigned)batch.count), dim3(256), 0, st, batch, len, stride, scratch);
+  });
   const int nk = (p.sh_degree + 1) * (p.sh_degree + 1);
   auto permute_tensor = [&](const gs_params& t, int64_t len) {
     float* rows_of[5] = {t.mean, t.log_scale, t.quat, t.opacity_logit, t.sh};
     const int count[5] = {3, 3, 4, 1, 3 * nk};
     for (int g = 0; g < 5; ++g)
-      for (int r = 0; r < count[g]; ++r) permute(reinterpret_cast<uint32_t*>(rows_of[g] + (int64_t)r * len), len);
+      for (int r = 0; r < count[g]; ++r) rows.add(reinterpret_cast<uint32_t*>(rows_of[g] + (int64_t)r * len), len);
   };
   permute_tensor(p, n);
   if (base) permute_tensor(*base, n);
-  if (ids) permute(ids, n);
-  permute(cell_of, n);
+  if (ids) rows.add(ids, n);
+  rows.add(cell_of, n);
   // the active prefix maps onto itself (pool bit above the cell), so the
   // moments take the permutation's first n_active entries
   if (m) permute_tensor(*m, n_active);
   if (v) permute_tensor(*v, n_active);
-  flush();
+  rows.flush();
   return hipGetLastError();
 }
 

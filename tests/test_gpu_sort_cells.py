@@ -108,3 +108,62 @@ def test_grouping_between_steps_keeps_graph_valid():
             close = np.abs(a - b) <= 1e-5 + 1e-4 * np.abs(a)
             assert close.mean() > 0.99
         assert abs(eager.loss.item() - graph.loss.item()) <= 1e-3 * eager.loss.item()
+
+
+class _Emptied:
+    """Moments after everything was frozen, as a caller of the C ABI describes
+    them: the same storage, with n = 0."""
+
+    def __init__(self, dp):
+        self.dp = dp
+
+    def struct(self):
+        s = self.dp.struct()
+        s.n = 0
+        return s
+
+
+@pytest.mark.parametrize("degree", [1, 2, 3])
+def test_empty_active_pool_keeps_its_moment_storage(oracle, degree):
+    n, n_cells = 5000, 97
+    w = S.small_workload(141, n, 1.0, degree, [(64, 48)], dist=3.0)
+    r = renderer_for(w)
+    P = DeviceParams.from_scene(w.scene)
+    m, v = (DeviceParams(*[torch.full_like(t, x) for t in P.tensors()], degree) for x in (0.25, 0.5))
+    cells_np = np.random.default_rng(degree).integers(0, n_cells, n).astype(np.uint32)
+    cells = torch.from_numpy(cells_np.view(np.int32)).cuda()
+    p0 = _rows(P, n)
+    r.ctx.sort_cells(P, cells, n_cells, r.ws, m=_Emptied(m), v=_Emptied(v))
+    torch.cuda.synchronize()
+    order = oracle.cell_order(cells_np, 0, n_cells)
+    for a, e in zip(_rows(P, n), p0):
+        assert np.array_equal(a, e[:, order])
+    assert np.array_equal(cells.cpu().numpy().view(np.uint32), cells_np[order])
+    assert all(bool((t == x).all()) for d, x in ((m, 0.25), (v, 0.5)) for t in d.tensors())
+
+
+def test_whole_batches_of_rows(oracle):
+    """A plan of eight views holds more than 64 rows of scratch, so that the
+    rows of model and baseline (120 with the columns) and those of the moments
+    (118) move in full batches of 64."""
+    n, na, n_cells = 3001, 2003, 61
+    w = S.small_workload(142, n, 1.0, 3, [(32, 32)] * 8, dist=3.0)
+    r = renderer_for(w)
+    P = DeviceParams.from_scene(w.scene)
+    base = DeviceParams(*[t + 0.5 for t in P.tensors()], 3)
+    rng = np.random.default_rng(5)
+    mk = lambda: DeviceParams(*[torch.from_numpy(rng.normal(size=t.shape[:-1] + (na,)).astype(F32)).cuda()
+                                for t in P.tensors()], 3)
+    m, v = mk(), mk()
+    ids = torch.arange(n, dtype=torch.int32, device="cuda")
+    cells_np = rng.integers(0, n_cells, n).astype(np.uint32)
+    cells = torch.from_numpy(cells_np.view(np.int32)).cuda()
+    full, active = _rows(P, n) + _rows(base, n), _rows(m, na) + _rows(v, na)
+    r.ctx.sort_cells(P, cells, n_cells, r.ws, m=m, v=v, ids=ids, baseline=base)
+    torch.cuda.synchronize()
+    order = oracle.cell_order(cells_np, na, n_cells)
+    for a, e in zip(_rows(P, n) + _rows(base, n), full):
+        assert np.array_equal(a, e[:, order])
+    for a, e in zip(_rows(m, na) + _rows(v, na), active):
+        assert np.array_equal(a, e[:, order[:na]])
+    assert np.array_equal(ids.cpu().numpy(), order.astype(np.int32))
