@@ -19,6 +19,7 @@
 // All kernels are driven by device-side counts so the stage can be captured
 // in a graph: grids are sized for the plan's capacity and idle blocks exit.
 #include "internal.h"
+#include "list_route.h"
 
 namespace gs {
 namespace {
@@ -1162,14 +1163,6 @@ __global__ __launch_bounds__(256) void k_order_scatter(const uint2* ranges, uint
 // each tile the pairs whose rectangle covers it, and k_small_fill writes them
 // in order behind those of the tiles before.
 constexpr uint32_t kInvisible = 0xffffffffu;   // above the bits of every depth
-// Bounds of that route: where it stops being the faster one (us per build,
-// compared / sorted, 16x16 tiles): 1000 Gaussians in one view of 64 tiles
-// 15 / 81; 8192 in 4 views of 676 tiles 64 / 123; 12,000 in 4 of 1764 113 / 144;
-// 16,000 in 4 of 676 157 / 125; 4096 in 1 of 8160 95 / 147; 3000 in 4 of 14,400
-// 147 / 152; 24,000 in 1 of 361 115 / 117.
-constexpr int64_t kSmallN = 16384;                 // Gaussians
-constexpr int64_t kSmallCompares = 1ll << 29;      // compares of the ranking, all views
-constexpr int64_t kSmallCovers = 1ll << 25;        // (tile, Gaussian) pairs
 
 // A workgroup ranks 64 pairs of a view, its kRankWaves wavefronts counting an
 // equal part of the view's pairs each (one compare and one add of the carry
@@ -1451,11 +1444,11 @@ static hipError_t order_tiles(const Plan& pl, void* ws, int32_t tile_begin, int6
   return hipGetLastError();
 }
 
-// Whether the call's lists are built by comparing everything with everything.
+// Whether the call's lists are built by comparing everything with everything:
+// where that is the faster route, and the tile counts fit the scratch that is
+// free then (a few words per tile, short only for a tiny key capacity).
 static bool small_lists(const Plan& pl, int nv, int64_t ntiles) {
-  const int64_t n = pl.n;
-  return n <= kSmallN && n * n * nv <= kSmallCompares && n * ntiles <= kSmallCovers &&
-         4 * NW * ntiles <= (int64_t)(pl.ws.vals_a - pl.ws.vrect_b);   // the tile counts' scratch
+  return compares_all(pl.n, nv, ntiles) && 4 * NW * ntiles <= (int64_t)(pl.ws.vals_a - pl.ws.vrect_b);
 }
 
 hipError_t launch_tile_lists(const Plan& pl, int v0, int nv, void* ws, hipStream_t st) {

@@ -137,6 +137,24 @@ def test_tile_lists_either_side_of_the_small_model_bounds(oracle, n, sizes, tile
     assert np.array_equal(seg_np(r, "ranges", np.uint32).reshape(-1, 2), ranges_o)
 
 
+@pytest.mark.parametrize("n,sizes", [
+    (100, ((1568, 1584),)),                                  # compared: 9702 tiles
+    (100, ((1568, 1600),)), (1000, ((3840, 2160),)),         # sorted: 9800 and 32,400 tiles
+    (400, ((1920, 1080),) * 8)])                             # sorted: 65,280 tiles
+def test_tile_lists_of_small_models_in_large_frames(oracle, n, sizes):
+    w = small(seed=152, n=n, sizes=sizes)
+    w.scene.log_scale[:, :2] = -0.5
+    r = renderer_for(w, cap=1 << 21)                         # room for the counts of all these tiles
+    P = DeviceParams.from_scene(w.scene)
+    r.ctx.project(P, r.dev_cams, 0, r.n_views, r.ws)
+    r.ctx.build_tile_lists(0, r.n_views, r.ws)
+    c = r.counters()
+    vals_o, ranges_o = oracle.tile_lists(w.scene, w.cams, 16, 16)
+    assert c.overflow == 0 and c.keys == len(vals_o)
+    assert np.array_equal(seg_np(r, "sorted_values", np.uint32)[:c.keys], vals_o)
+    assert np.array_equal(seg_np(r, "ranges", np.uint32).reshape(-1, 2), ranges_o)
+
+
 @pytest.mark.parametrize("cap", [1 << 20, 1 << 22])   # histograms read as they are / scanned
 @pytest.mark.parametrize("n,sizes,tile", [
     (16385, ((64, 48),), (8, 8)),              # 6 tile bits: the first pass's buckets are the tiles
