@@ -266,18 +266,28 @@ struct ProjArgs {
 };
 
 // Visible lanes from which a wavefront stores the entries of all of its lanes
-// (a wavefront's 256 bytes of a 4-byte array are two lines or more). What
-// counts is that wavefronts in full view write whole lines: 1, 4 and 12 measure
-// the same, with 12 a nearly empty wavefront writes only its own entries.
-constexpr int kWholeLanes = 12;
+// (a wavefront's 256 bytes of a 4-byte array are two lines or more).  With few
+// visible lanes the other lanes' entries cost more than the partly written
+// lines, the more so where the records go past the caches; each line lies where
+// no part of visible Gaussians is slower than with their entries alone.  1M
+// Gaussians in random order, SH degree 0.  Eight views, past the caches (us at
+// 12, 20, 24, 28 and 64 lanes): 15% visible 101, 87, 86, 86, 90; 20% 109, 87,
+// 86, 86, 89; 25% 107, 91, 113, 118, 120; 30% 106, 110, 121, 157, 164; 50% 105,
+// 103, 104, 109, 233; all 106.  Four views, in the caches (at 4, 12, 24 and 64):
+// 5% 50, 47, 48, 47; 15% 59, 55, 55, 55; 25% 59, 60, 65, 66; 50% 60, 60, 60, 82.
+constexpr int kWholeLanes = 12, kWholeLanesStreamed = 20;
 
 constexpr int kViewWaves = 1;   // (the per-Gaussian view mask assumes a single wavefront per Gaussian)
 static_assert(kViewWaves == 1, "one wavefront writes a Gaussian's view mask");
 
-// kCells: with preculling.
+// kCells: with preculling.  Bound by its stores: at degree 3 a fourth wavefront
+// per SIMD only widens the set of lines written in parts (four views, 25%
+// visible: 82 us at three, 83 at four; eight views, 5%: 107 and 114).
 template <int DEG, bool kCells>
-__global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+__global__ __launch_bounds__(64 * kViewWaves) __attribute__((amdgpu_waves_per_eu(3, DEG < 3 ? 6 : 3)))
+void k_project(ProjArgs a) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
   // uniform, so that the per-view camera is read with scalar loads
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t n = a.p.n;
@@ -299,15 +309,18 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
   }
   // SH coefficients: the first kShRegs in registers, the rest parked in this
   // wavefront's own LDS columns (each lane reads back only what it wrote, so
-  // no barrier is needed); with all 48 there and the records' staging beside
-  // them, a compute unit would hold 10 wavefronts instead of 13
-  constexpr int kShRegs = 3 * nk < 11 ? 3 * nk : 11;
+  // no barrier is needed); with all 48 of degree 3 there and the records'
+  // staging beside them, a compute unit would hold 10 wavefronts instead of 12
+  constexpr int kShRegs = DEG == 3 ? 11 : 0;
   constexpr int kShLds = 3 * nk - kShRegs;
   __shared__ float s_sh[kViewWaves][kShLds ? kShLds : 1][64];
   __shared__ float4 s_rec[kViewWaves][3 * 64];
-  const int lane = threadIdx.x & 63;
+  // a lane's record goes to its place in s_rec as it is computed (kStaged), or is
+  // held until the wavefront's stores: 68 / 70 us at degree 0 (eight views, 2%
+  // visible), but 86 / 82 at degree 3 (four views, 25%)
+  constexpr bool kStaged = DEG < 3;
   bool sh_ok = true;
-  float sh_reg[kShRegs];
+  float sh_reg[kShRegs ? kShRegs : 1];
   Gauss g;
   g.ok = false;
   if (any) {
@@ -321,15 +334,19 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
     load_gauss(a.p, i, g, sh_ok);
   }
   uint64_t vm = 0ull;
-  const int lanes = (int)(n - (i - lane) < 64 ? n - (i - lane) : 64);   // of this wavefront that hold a Gaussian
+  const bool full = i0 + 64 <= n;   // every lane holds a Gaussian
 #pragma unroll 1
   for (int v = a.v0 + wave; v < a.v0 + a.nv; v += kViewWaves) {
-    const int64_t o = (int64_t)v * n + i;
+    const int64_t o = (int64_t)v * n + i0;   // uniform: the wavefront's first entry of the view
     const gs_camera cam = read_camera(a.cams, v);
     uint32_t cnt = 0;
     uint2 rect = make_uint2(0u, 0u);
     uint32_t depth = 0;
-    float4 r0 = make_float4(0.f, 0.f, 0.f, 0.f), r1 = r0, r2 = r0;
+    float4 held[3] = {};
+    auto put = [&](int q, const float4& part) {
+      if constexpr (kStaged) s_rec[wave][lane * 3 + q] = part;
+      else held[q] = part;
+    };
     if (g.ok && (!kCells || a.cell_mask[(int64_t)v * a.cell_row + cell])) {
       const float z32 = depth_key(cam.R[6], cam.R[7], cam.R[8], cam.t[2], g.mu[0], g.mu[1], g.mu[2]);
       ViewGeom vg;
@@ -350,10 +367,12 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
           // splat record
           const float uh = (float)vg.u, wh = (float)vg.w;
           const float ul = (float)(vg.u - (double)uh), wl = (float)(vg.w - (double)wh);
+          put(0, make_float4(uh, wh, ul, wl));
           const double iC = 1.0 / vg.C;
           const float qa = (float)(vg.C / vg.det);
           const float qr = (float)(-vg.B * iC);
           const float qs = (float)iC;
+          put(1, make_float4(qa, qr, qs, g.o));
           float d[3], len;
           view_dir(cam, g.mu, d, &len);
           float Y[16];
@@ -369,9 +388,7 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
             }
             col[ch] = fmaxf(s, 0.f);
           }
-          r0 = make_float4(uh, wh, ul, wl);
-          r1 = make_float4(qa, qr, qs, g.o);
-          r2 = make_float4(col[0], col[1], col[2], 0.f);
+          put(2, make_float4(col[0], col[1], col[2], 0.f));
         }
       }
     }
@@ -382,36 +399,35 @@ __global__ __launch_bounds__(64 * kViewWaves) void k_project(ProjArgs a) {
     // records through LDS so that each store covers whole lines, past the
     // caches when all of them exceed the last one: 252 us.
     const uint64_t seen = __ballot(cnt != 0u);
-    const bool whole = __popcll(seen) >= kWholeLanes;   // uniform
+    const bool whole = full && __popcll(seen) >= (a.stream_rec ? kWholeLanesStreamed : kWholeLanes);   // uniform
     if (whole || cnt != 0u) {
-      a.rect[o] = rect;
-      a.depth[o] = depth;
+      (a.rect + o)[lane] = rect;
+      (a.depth + o)[lane] = depth;
     }
+    if (!kStaged && whole) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) s_rec[wave][lane * 3 + q] = held[q];
+    }
+    __builtin_amdgcn_wave_barrier();
     if (whole) {
-      s_rec[wave][lane * 3 + 0] = r0;
-      s_rec[wave][lane * 3 + 1] = r1;
-      s_rec[wave][lane * 3 + 2] = r2;
-      __builtin_amdgcn_wave_barrier();
-      // the wavefront's records in pieces of 16 bytes (lanes past the last
-      // Gaussian have left: the lanes here store all pieces there are)
+      // the wavefront's records in pieces of 16 bytes
       typedef float F4 __attribute__((ext_vector_type(4)));
       const F4* src = reinterpret_cast<const F4*>(&s_rec[wave][0]);
-      F4* dst = reinterpret_cast<F4*>(a.rec + (o - lane) * 3);
+      F4* dst = reinterpret_cast<F4*>(a.rec + o * 3);
       if (a.stream_rec) {   // uniform
 #pragma unroll
-        for (int q = 0; q < 3; ++q) __builtin_nontemporal_store(src[q * lanes + lane], dst + q * lanes + lane);
+        for (int q = 0; q < 3; ++q) __builtin_nontemporal_store(src[q * 64 + lane], dst + q * 64 + lane);
         asm volatile("");   // (the two forms would be merged into ordinary stores)
       } else {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) dst[q * lanes + lane] = src[q * lanes + lane];
+        for (int q = 0; q < 3; ++q) dst[q * 64 + lane] = src[q * 64 + lane];
       }
-      __builtin_amdgcn_wave_barrier();
     } else if (cnt != 0u) {
-      a.rec[o * 3 + 0] = r0;
-      a.rec[o * 3 + 1] = r1;
-      a.rec[o * 3 + 2] = r2;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) (a.rec + o * 3)[lane * 3 + q] = kStaged ? s_rec[wave][lane * 3 + q] : held[q];
     }
-    a.count[o] = cnt;
+    __builtin_amdgcn_wave_barrier();
+    (a.count + o)[lane] = cnt;
     if (cnt != 0u) vm |= a.nv <= 64 ? 1ull << (v - a.v0) : ~0ull;
   }
   a.vmask[i] = vm;

@@ -236,6 +236,30 @@ def test_records_around_the_whole_line_rule(n, keep, deg):
     assert np.array_equal(seg_np(r2, "depth", np.uint32).reshape(2, n)[left], depth[left])
 
 
+@pytest.mark.parametrize("keep", [1, 11, 12, 23, 24, 25, 64])
+def test_streamed_records_around_the_whole_line_rule(keep):
+    """The same where all records exceed the last-level cache and are stored
+    past it (23 views of 250,000 Gaussians, 276 MB)."""
+    n, views = 250_007, 23
+    w = small(seed=165, n=n, sizes=((64, 48),) * views, deg=0)
+    sc = w.scene
+    r = renderer_for(w, cap=1 << 16)
+    drop = np.arange(n) % 64 >= keep           # leave `keep` lanes of each wavefront
+    got = []
+    for s in (False, True):
+        if s:
+            sc.mean[:, drop] = np.nan
+        P = DeviceParams.from_scene(sc)
+        r.ctx.project(P, r.dev_cams, 0, views, r.ws)
+        rec = r.ctx.segment(r.ws, "record").view(torch.float32).view(views, n, 12)
+        cols = [r.ctx.segment(r.ws, k).view(torch.int32).view(views, n, -1) for k in ("rect", "depth", "count")]
+        got.append([rec.clone()] + [c.clone() for c in cols])
+    kept = torch.from_numpy(~drop).cuda() & (got[0][3][:, :, 0] > 0)
+    assert torch.equal(got[1][3][:, :, 0] > 0, kept) and int(kept.sum()) > n // 64
+    for a, b in zip(got[0], got[1]):
+        assert torch.equal(a[kept], b[kept])
+
+
 @pytest.mark.parametrize("bg", [(0.0, 0.0, 0.0), (0.3, 0.5, 0.1)])
 def test_composite_matches_oracle(oracle, bg):
     w = small(seed=103)
