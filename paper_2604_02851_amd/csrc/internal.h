@@ -11,6 +11,7 @@ namespace gs {
 
 constexpr int kMaxViews = 256;
 constexpr int kRecFloats = 12;    // splat record: 3 x float4
+constexpr int64_t kLastCacheBytes = 256ll << 20;
 constexpr int kG2Fields = 9;      // screen-space gradient fields per (view, Gaussian), one plane each
 constexpr int kSortBlock = 512;   // threads of the sort / scan kernels
 constexpr int kSortItems = 8;     // keys per thread per chunk

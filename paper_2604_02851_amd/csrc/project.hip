@@ -702,7 +702,7 @@ hipError_t launch_project(const Plan& pl, const ParamPtrs& p, const gs_camera* c
   a.count = seg<uint32_t>(ws, pl.ws.count);
   a.rect = seg<uint2>(ws, pl.ws.rect);
   a.rec = seg<float4>(ws, pl.ws.rec);
-  a.stream_rec = (int64_t)nv * p.n * (int64_t)(sizeof(float) * kRecFloats) > (256ll << 20);
+  a.stream_rec = (int64_t)nv * p.n * (int64_t)(sizeof(float) * kRecFloats) > kLastCacheBytes;
   a.vmask = seg<uint64_t>(ws, pl.ws.vmask);
   a.cell_of = pl.cell_of;
   a.cell_mask = pl.cell_mask;

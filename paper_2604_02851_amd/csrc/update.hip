@@ -144,6 +144,7 @@ struct DeltaArgs {
   uint32_t* bcount;   // [6][nb], scanned in place
   uint32_t* dbase;    // [0..5] section base, [6..11] count, [15] total
   int32_t nb;
+  bool stream_rest;         // the higher SH bands and their baseline exceed the last-level cache
   uint32_t* out;
 };
 
@@ -175,29 +176,64 @@ __device__ __forceinline__ bool element_sent(const CodecDev& c, int g, float p, 
   return quant_code(p, c.lo[g], c.inv[g], c.bits[g]) != quant_code(b, c.lo[g], c.inv[g], c.bits[g]);
 }
 
-// Bit q set when Gaussian i + q's row of group g is sent (q < 4, i + q < n).
-// Whole quads are read 16 bytes at a time, at any word alignment, and every
-// row of the group whatever the rows before it showed: a test that ends at the
-// first hit waits for each row's values before it asks for the next (all groups
-// of 3M Gaussians 311 us, 4.5 TB/s; now 245).  kStream, for the group of the
-// higher SH bands, keeps its 1.1 GB of such a frame from evicting what the
-// kernels after this one read again; the small groups stay cached for them.
+// Whether a Gaussian is sent is the comparison of all rows of a group; what
+// bounds it is how many of those are read, and how many are in flight.  Whole
+// quads are read 16 bytes at a time, at any word alignment: the first row of
+// every group together; then, of a group in which a wavefront has a Gaussian
+// that its first row does not send, the others, kRowsAtOnce at a time until all
+// of them are sent.  A test that ends at each Gaussian's first hit waits for
+// each row's values before it asks for the next; one that reads every row
+// whatever the first shows pays for them where everything changed (all groups
+// of 3M Gaussians encoded, us: nothing changed 312 and 246, now 242; everything
+// 670 and 922, now 683; 8 or 11 rows at once measure the same, and up to 10%
+// slower for 500k).  kStream, for higher SH bands that exceed the last cache,
+// keeps them from evicting what the kernels after this one read again; rows
+// that fit it stay cached for those (100k Gaussians, 90% sent raw: 62 us, 82
+// when streamed).
 typedef V4 V4Unaligned __attribute__((aligned(4)));
+constexpr int kRowsAtOnce = 4;
+
+template <bool kStream>
+__device__ __forceinline__ V4 load_quad(const float* p) {
+  const V4Unaligned* q = reinterpret_cast<const V4Unaligned*>(p);
+  return kStream ? __builtin_nontemporal_load(q) : *q;
+}
+
+template <int MODE>
+__device__ __forceinline__ uint32_t quad_sent(const CodecDev& c, int g, const V4& p, const V4& b) {
+  uint32_t hit = 0u;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) hit |= element_sent<MODE>(c, g, p[q], b[q]) ? 1u << q : 0u;
+  return hit;
+}
+
+__device__ __forceinline__ uint32_t quad_sent(const CodecDev& c, int g, const V4& p, const V4& b) {
+  const int md = c.mode[g];
+  if (md == 0) return quad_sent<0>(c, g, p, b);
+  return md == 1 ? quad_sent<1>(c, g, p, b) : quad_sent<2>(c, g, p, b);
+}
+
+// Bit q set when Gaussian i + q's row of group g is sent (q < 4, i + q < n):
+// `hit`, which holds those that the first row sends, and what the rows from
+// the second on add (all of them for the last, partly filled quad).
 template <int MODE, bool kStream>
-__device__ __forceinline__ uint32_t rows_sent(const DeltaArgs& a, int g, int64_t i) {
+__device__ __forceinline__ uint32_t rows_sent(const DeltaArgs& a, int g, int64_t i, uint32_t hit) {
   const float* cur = a.g.cur[g] + i;
   const float* base = a.g.base[g] + i;
   const int width = a.g.width[g];
-  uint32_t hit = 0u;
   if (i + 4 <= a.n) {
-#pragma unroll 4
-    for (int k = 0; k < width; ++k) {
-      const V4Unaligned* pp = reinterpret_cast<const V4Unaligned*>(cur + (int64_t)k * a.n);
-      const V4Unaligned* pb = reinterpret_cast<const V4Unaligned*>(base + (int64_t)k * a.n);
-      const V4 p = kStream ? __builtin_nontemporal_load(pp) : *pp;
-      const V4 b = kStream ? __builtin_nontemporal_load(pb) : *pb;
+    for (int k = 1; k < width; k += kRowsAtOnce) {
+      if (__ballot(hit != 15u) == 0ull) break;   // uniform
+      V4 p[kRowsAtOnce], b[kRowsAtOnce];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) hit |= element_sent<MODE>(a.c, g, p[q], b[q]) ? 1u << q : 0u;
+      for (int q = 0; q < kRowsAtOnce; ++q) {
+        if (k + q >= width) continue;   // uniform
+        p[q] = load_quad<kStream>(cur + (int64_t)(k + q) * a.n);
+        b[q] = load_quad<kStream>(base + (int64_t)(k + q) * a.n);
+      }
+#pragma unroll
+      for (int q = 0; q < kRowsAtOnce; ++q)
+        if (k + q < width) hit |= quad_sent<MODE>(a.c, g, p[q], b[q]);
     }
   } else {
     for (int k = 0; k < width; ++k)
@@ -208,23 +244,37 @@ __device__ __forceinline__ uint32_t rows_sent(const DeltaArgs& a, int g, int64_t
 }
 
 template <bool kStream>
-__device__ __forceinline__ uint32_t group_sent(const DeltaArgs& a, int g, int64_t i) {
+__device__ __forceinline__ uint32_t group_sent(const DeltaArgs& a, int g, int64_t i, uint32_t hit) {
   const int md = a.c.mode[g];
-  if (md == 0) return rows_sent<0, kStream>(a, g, i);
-  return md == 1 ? rows_sent<1, kStream>(a, g, i) : rows_sent<2, kStream>(a, g, i);
+  if (md == 0) return rows_sent<0, kStream>(a, g, i, hit);
+  return md == 1 ? rows_sent<1, kStream>(a, g, i, hit) : rows_sent<2, kStream>(a, g, i, hit);
 }
 
 // A thread takes four Gaussians, a wavefront the 256 of one block of the
 // counts.
-__global__ __launch_bounds__(256) void k_delta_flags(DeltaArgs a) {
-  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+__global__ __launch_bounds__(64) void k_delta_flags(DeltaArgs a) {
+  const int64_t i = ((int64_t)blockIdx.x * 64 + threadIdx.x) * 4;
   const int lane = threadIdx.x & 63;
-  const int64_t block = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t block = blockIdx.x;
   uint32_t f[4] = {0u, 0u, 0u, 0u};
+  uint32_t first = 0u;   // bits 4 g + q: group g's first row sends Gaussian i + q
+  if (i + 4 <= a.n) {
+    V4 p[6], b[6];
+#pragma unroll
+    for (int g = 0; g < 6; ++g) {
+      if (!((a.mask >> g) & 1u) || a.g.width[g] == 0) continue;   // uniform
+      p[g] = load_quad<false>(a.g.cur[g] + i);
+      b[g] = load_quad<false>(a.g.base[g] + i);
+    }
+#pragma unroll
+    for (int g = 0; g < 6; ++g)
+      if (((a.mask >> g) & 1u) && a.g.width[g] != 0) first |= quad_sent(a.c, g, p[g], b[g]) << (4 * g);
+  }
+#pragma unroll 1
   for (int g = 0; g < 6; ++g) {
-    uint32_t hit = 0u;
+    uint32_t hit = (first >> (4 * g)) & 15u;
     if (((a.mask >> g) & 1u) && i < a.n)
-      hit = g == 2 ? group_sent<true>(a, g, i) : group_sent<false>(a, g, i);
+      hit = g == 2 && a.stream_rest ? group_sent<true>(a, g, i, hit) : group_sent<false>(a, g, i, hit);
     uint32_t count = 0u;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -571,9 +621,10 @@ static hipError_t run_delta(DeltaArgs& a, const DeltaScratch& s, hipStream_t st)
   a.flags = s.flags;
   a.bcount = s.bcount;
   a.dbase = s.dbase;
+  a.stream_rest = 8 * a.n * a.g.width[2] > kLastCacheBytes;
   a.nb = (int32_t)((a.n + 255) / 256);
   if (a.nb > s.max_blocks) return hipErrorInvalidValue;
-  if (a.nb > 0) hipLaunchKernelGGL(k_delta_flags, dim3((a.nb + 3) / 4), dim3(256), 0, st, a);
+  if (a.nb > 0) hipLaunchKernelGGL(k_delta_flags, dim3(a.nb), dim3(64), 0, st, a);
   hipError_t e = launch_scan(a.bcount, a.bcount, 6ll * a.nb, nullptr, s.partial, s.partial_len, a.dbase + 15, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_delta_header, dim3(1), dim3(64), 0, st, a);

@@ -218,3 +218,40 @@ def test_empty_mask_and_empty_model(oracle):
     r0.ctx.delta_extract(e0, e0.clone(), 0x3F, 1e-3, raw0, r0.ws)
     torch.cuda.synchronize()
     assert raw0.cpu().numpy().tolist() == [0] * 6
+
+
+@pytest.mark.parametrize("name", ["default", "raw", "mixed"])
+@pytest.mark.parametrize("deg", [0, 1, 3])
+def test_encode_by_rows_that_changed(oracle, name, deg):
+    """Wavefronts (256 Gaussians) whose rows all send every Gaussian, whose
+    first row sends all but one, which send nothing, and which send by one
+    later row only (the second, fifth, sixth, last), with a ragged end."""
+    n = 256 * 8 + 131
+    codecs = CODEC_SETS[name]
+    w, r = _setup(n, deg, 3)
+    base_h, cur_h = w.scene, w.scene.copy()
+    for _, t in cur_h.tensors():
+        rows = t.reshape(-1, n)
+        if rows.shape[0] == 3 * (deg + 1) ** 2 and rows.shape[0] > 3:
+            parts = [rows[:3], rows[3:]]       # DC and the higher bands are groups of their own
+        else:
+            parts = [rows]
+        for g in parts:
+            g[:, :256] += F32(0.25)
+            g[0, 256:512] += F32(0.25)
+            g[0, 300] -= F32(0.25)
+            g[-1, 300] += F32(0.25)
+            for b, k in enumerate((1, 4, 5, len(g) - 1)):
+                g[min(k, len(g) - 1), 768 + 256 * b:1024 + 256 * b] += F32(0.25)
+            g[0, 1792:2048:3] += F32(0.25)
+            g[-1, 2048:] += F32(0.25) * (np.arange(n - 2048) % 2).astype(F32)
+    cur, base = DeviceParams.from_scene(cur_h), DeviceParams.from_scene(base_h)
+    epoch = torch.tensor([9], dtype=torch.int32, device="cuda")
+    out = torch.zeros(N.codec_capacity_words(n, deg, codecs, 0x3F), dtype=torch.int32, device="cuda")
+    r.ctx.delta_encode(cur, base, codecs, 0x3F, epoch, out, r.ws)
+    torch.cuda.synchronize()
+    ref_base = base_h.copy()
+    ref = oracle.delta_encode(cur_h, ref_base, codecs, 0x3F, epoch=9)
+    got = out.cpu().numpy().view(np.uint32)
+    assert np.array_equal(got[:len(ref)], ref)
+    assert _same(_host(base), ref_base)
