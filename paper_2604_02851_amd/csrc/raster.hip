@@ -795,8 +795,10 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs& a, uint32_t sl
             g[k][8] = fmaf(at, G2[q], g[k][8]);
             const float diff = fmaf(r2[k].z, G2[q], fmaf(r2[k].y, G1[q], r2[k].x * G0[q])) - SG[q];
             SG[q] = fmaf(alt, diff, SG[q]);
-            // dL/dalpha dalpha/dP; the clamp cuts alpha off from opacity and power
-            const float W = __builtin_amdgcn_inverse_ballot_w64(clamped[k]) ? 0.f : at * diff;
+            // dL/dalpha dalpha/dP; the clamp cuts alpha off from opacity and power.
+            // (Selected rather than left to alpha 0: an infinite or NaN upstream
+            // gradient at a pixel that does not take the splat is no part of it.)
+            const float W = __builtin_amdgcn_inverse_ballot_w64(take & ~clamped[k]) ? at * diff : 0.f;
             g[k][5] += W;
             g[k][0] = fmaf(W, sg[k].e, g[k][0]);
             const float tx_ = W * sg[k].dx, ty_ = W * sg[k].dy;

@@ -597,3 +597,35 @@ def test_delta_bit_exact(oracle):
     assert epoch.item() == 1
     for a, b in zip(Pb.tensors(), Pc.tensors()):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+@pytest.mark.parametrize("tile,ppt,wave_w", [((8, 8), 1, 8), ((16, 16), 1, 16), ((32, 16), 2, 32), ((32, 32), 4, 16)])
+def test_nonfinite_upstream_stays_with_its_pixel(tile, ppt, wave_w, bad):
+    """An infinite or NaN upstream gradient at one pixel reaches the geometry
+    and opacity of the Gaussians composited there, and of no others: theirs are
+    those of a zero at that pixel."""
+    w = small(seed=190, n=1500, deg=0, sizes=((96, 64),))
+    w.scene.opacity_logit[::7] = 6.0           # some reach the alpha clamp
+    r = renderer_for(w, tile=tile, ppt=ppt, wave_w=wave_w)
+    P = DeviceParams.from_scene(w.scene)
+    img = r.forward(P)[0]
+    up = torch.from_numpy(_up(w)).view(3, 64, 96)
+    y, x = 37, 41
+
+    def grads(u):
+        g = DeviceParams.zeros_like(P)
+        r.backward(P, u.reshape(-1).cuda(), 0, g)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy().reshape(-1, 1500) for t in g.tensors()[:4]]
+
+    only = torch.zeros_like(up)
+    only[:, y, x] = 1.0
+    there = np.any([np.any(t != 0, 0) for t in grads(only)], 0)
+    assert 3 <= there.sum() < 200
+    without, with_bad = up.clone(), up.clone()
+    without[:, y, x], with_bad[:, y, x] = 0.0, bad
+    for a, b in zip(grads(with_bad), grads(without)):
+        a, b = a[:, ~there], b[:, ~there]
+        assert np.isfinite(a).all()
+        assert np.abs(a - b).max() <= 1e-4 * np.abs(b).max()   # the order of the atomic sums
