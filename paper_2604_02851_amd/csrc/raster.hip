@@ -537,11 +537,13 @@ __global__ __launch_bounds__(TW* TH / PPT) __attribute__((amdgpu_waves_per_eu(8)
 
 // Persistent (schedules 2 and 3): as many workgroups as fit on the chip at
 // once, each taking the call's tiles from the work queue until it is empty.
-// The loop around the tile body costs the compiler a few registers; held to
-// the grid kernel's seven wavefronts per SIMD (a few bytes spilled) it
-// measured faster than at six.
+// Held to eight wavefronts per SIMD like the grid kernel: at four pixels per
+// lane the loop around the tile body then spills three to seven registers, and
+// still every shape is at least as fast as at seven (1M Gaussians, four views of
+// 1280x720, batches of 64: 32x32 tiles at one pixel per lane 792 us instead of
+// 1174, at two 452 and 498, at four 388 and 408).
 template <int TW, int TH, int PPT, int SW, int BATCH>
-__global__ __launch_bounds__(TW* TH / PPT) __attribute__((amdgpu_waves_per_eu(7))) void k_composite_persistent(
+__global__ __launch_bounds__(TW* TH / PPT) __attribute__((amdgpu_waves_per_eu(8))) void k_composite_persistent(
     CompArgs a) {
   __shared__ FwdShared<BATCH, (Geom<TW, TH, PPT, SW>::NWAVES >= 2 ? 2u : 1u)> sm;
   __shared__ uint32_t s_next;
