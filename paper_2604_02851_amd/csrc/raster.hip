@@ -582,16 +582,25 @@ struct BwdArgs {
 };
 
 // LDS of one compositing workgroup (adjoint).
-template <int BATCH>
+template <int BATCH, int NWAVES>
 struct BwdShared {
+  // splats whose sums are kept at a time: the batch's, over the tile's
+  // wavefronts; those of each 64 that a lone wavefront works on, as with 256 it
+  // would have 6 instead of 9 workgroups per compute unit (1M Gaussians, four
+  // views of 1280x720, batches of 256: 16x16 tiles at four pixels per lane 1367
+  // instead of 1642 us, 16x8 at two 1924 and 2293)
+  static constexpr int SUMS = NWAVES == 1 && BATCH > 64 ? 64 : BATCH;
   float4 rec[BATCH * 3];
   uint32_t mask[BATCH];
   uint32_t id[BATCH];
-  // the batch's splat sums over the tile's wavefronts, field-major; the odd
-  // stride puts one splat's fields in different banks.  Zero between batches.
-  float g[9 * (BATCH + 1)];
+  // the splats' sums, field-major; the odd stride puts one splat's fields in
+  // different banks.  Zero between batches.
+  float g[9 * (SUMS + 1)];
   uint32_t max_last;
 };
+
+template <int TW, int TH, int PPT, int SW, int BATCH>
+using BwdSharedOf = BwdShared<BATCH, Geom<TW, TH, PPT, SW>::NWAVES>;
 
 // Adjoint of the compositing of one pixel, walked back to front from the
 // pixel's last composited splat (Sj = colour arriving from behind splat j,
@@ -608,8 +617,9 @@ struct BwdShared {
 // as the forward product's own rounding.
 // Adjoint of the compositing of tile `slot` of the call by the whole workgroup.
 template <int TW, int TH, int PPT, int SW, int BATCH>
-__device__ __forceinline__ void composite_bwd_tile(const BwdArgs& a, uint32_t slot, BwdShared<BATCH>& sm) {
+__device__ __forceinline__ void composite_bwd_tile(const BwdArgs& a, uint32_t slot, BwdSharedOf<TW, TH, PPT, SW, BATCH>& sm) {
   using G = Geom<TW, TH, PPT, SW>;
+  constexpr int SUMS = BwdSharedOf<TW, TH, PPT, SW, BATCH>::SUMS;
   constexpr int K = G::SPLATS;
   float4* s_rec = sm.rec;
   uint32_t* s_mask = sm.mask;
@@ -634,8 +644,8 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs& a, uint32_t sl
   const bool ninth = (lane & 15) == 15;
   const bool writer = (lane & 7) == 0 || ninth;
   const int my_field = reduce8_field(lane, lo8);   // by the whole wavefront
-  const int my_slot = (ninth ? 8 : my_field) * (BATCH + 1);
-  for (int q = threadIdx.x; q < 9 * (BATCH + 1); q += G::NT) s_g[q] = 0.f;
+  const int my_slot = (ninth ? 8 : my_field) * (SUMS + 1);
+  for (int q = threadIdx.x; q < 9 * (SUMS + 1); q += G::NT) s_g[q] = 0.f;
   if (threadIdx.x == 0) s_max = rg.x;
   __syncthreads();
   float G0[PPT], G1[PPT], G2[PPT], SG[PPT];
@@ -683,6 +693,34 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs& a, uint32_t sl
   __syncthreads();
   const uint32_t end_all = s_max;
   const bool all_active = a.n_active >= a.n_gauss;
+  // `count` splats' totals to the global planes, a wavefront per field (the two
+  // of the mean together, as both take the same sums); the LDS slots are left
+  // at zero.  Slot e holds splat e of the batch (or `base` - e, see SUMS).
+  auto flush = [&](int base, int count) {
+    for (int f = wave; f < 8; f += G::NWAVES) {   // uniform
+      for (int e = lane; e < count; e += 64) {
+        const int j = SUMS == BATCH ? e : base - e;
+        float* slot0 = s_g + e;
+        float* slot1 = s_g + (f + 1) * (SUMS + 1) + e;
+        const float4 r1 = s_rec[j * 3 + 1];   // staged: a and s carry -log2(e)/2
+        float* dst = a.g2 + s_id[j];
+        const float v = *slot1;
+        if (f == 0) {
+          const float me = *slot0;
+          if (me == 0.f && v == 0.f) continue;
+          const float ame = kMinus2Ln2 * r1.x * me;
+          atomicAdd(dst, ame);
+          atomicAdd(dst + a.g2_plane, fmaf(ame, r1.y, kMinus2Ln2 * r1.z * v));
+          *slot0 = 0.f;
+        } else {
+          if (v == 0.f) continue;
+          // d P / d conic = -1/2 dx^2, -dx dy, -1/2 dy^2; dP/do = 1/o per unit of alpha
+          atomicAdd(dst + (size_t)(f + 1) * a.g2_plane, f == 4 ? v / r1.w : f == 2 ? -v : f < 4 ? -0.5f * v : v);
+        }
+        *slot1 = 0.f;
+      }
+    }
+  };
   for (uint32_t b_end = end_all; b_end > rg.x;) {
     const uint32_t b_begin = (b_end - rg.x > (uint32_t)BATCH) ? b_end - BATCH : rg.x;
     const uint32_t cnt = b_end - b_begin;
@@ -832,36 +870,16 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs& a, uint32_t sl
 #pragma unroll
         for (int k = 0; k < K; ++k)
           if (taken[k] != 0ull) {   // uniform
-            if (writer) atomicAdd(s_g + my_slot + j[k], tot[k]);
+            if (writer) atomicAdd(s_g + my_slot + (SUMS == BATCH ? j[k] : base - j[k]), tot[k]);
           }
+      }
+      if (SUMS < BATCH) {
+        __syncthreads();
+        flush(base, min(base + 1, 64));
       }
     }
     __syncthreads();
-    // the batch's totals to the global planes, a wavefront per field (the two
-    // of the mean together, as both take the same sums); the LDS slots are
-    // left at zero for the next batch
-    for (int f = wave; f < 8; f += G::NWAVES) {   // uniform
-      for (uint32_t j = lane; j < cnt; j += 64) {
-        float* slot0 = s_g + j;
-        float* slot1 = s_g + (f + 1) * (BATCH + 1) + j;
-        const float4 r1 = s_rec[j * 3 + 1];   // staged: a and s carry -log2(e)/2
-        float* dst = a.g2 + s_id[j];
-        const float v = *slot1;
-        if (f == 0) {
-          const float me = *slot0;
-          if (me == 0.f && v == 0.f) continue;
-          const float ame = kMinus2Ln2 * r1.x * me;
-          atomicAdd(dst, ame);
-          atomicAdd(dst + a.g2_plane, fmaf(ame, r1.y, kMinus2Ln2 * r1.z * v));
-          *slot0 = 0.f;
-        } else {
-          if (v == 0.f) continue;
-          // d P / d conic = -1/2 dx^2, -dx dy, -1/2 dy^2; dP/do = 1/o per unit of alpha
-          atomicAdd(dst + (size_t)(f + 1) * a.g2_plane, f == 4 ? v / r1.w : f == 2 ? -v : f < 4 ? -0.5f * v : v);
-        }
-        *slot1 = 0.f;
-      }
-    }
+    if (SUMS == BATCH) flush(0, (int)cnt);
     __syncthreads();
     b_end = b_begin;
   }
@@ -874,7 +892,7 @@ __device__ __forceinline__ void composite_bwd_tile(const BwdArgs& a, uint32_t sl
 // One workgroup per tile (schedules 0 and 1).
 template <int TW, int TH, int PPT, int SW, int BATCH>
 __global__ __launch_bounds__(TW* TH / PPT) void k_composite_bwd(BwdArgs a) {
-  __shared__ BwdShared<BATCH> sm;
+  __shared__ BwdSharedOf<TW, TH, PPT, SW, BATCH> sm;
   composite_bwd_tile<TW, TH, PPT, SW, BATCH>(a, tile_of_block(blockIdx.x, (uint32_t)a.ntiles, a.schedule), sm);
 }
 
@@ -882,7 +900,7 @@ __global__ __launch_bounds__(TW* TH / PPT) void k_composite_bwd(BwdArgs a) {
 template <int TW, int TH, int PPT, int SW, int BATCH>
 __global__ __launch_bounds__(TW* TH / PPT) __attribute__((amdgpu_waves_per_eu(7))) void k_composite_bwd_persistent(
     BwdArgs a) {
-  __shared__ BwdShared<BATCH> sm;
+  __shared__ BwdSharedOf<TW, TH, PPT, SW, BATCH> sm;
   __shared__ uint32_t s_next;
   for (;;) {
     const uint32_t slot = queue_next(a.q, (uint32_t)a.ntiles, &s_next);

@@ -365,6 +365,26 @@ def test_backward_variants_match_oracle(oracle, tile, ppt, sw, schedule):
     assert rep["fail"] == 0
 
 
+@pytest.mark.parametrize("batch,schedule", [(32, 0), (128, 0), (256, 0), (256, 2)])
+@pytest.mark.parametrize("tile,ppt,sw", [((8, 8), 1, 8), ((16, 8), 2, 16), ((16, 16), 4, 16), ((16, 16), 1, 16)])
+def test_backward_by_batch_depth_matches_oracle(oracle, tile, ppt, sw, batch, schedule):
+    """Translucent splats in lists of several batches, the last one partial:
+    tiles of one wavefront send their sums every 64 splats, others every batch."""
+    w = small(seed=111, n=1500, sizes=((70, 50), (33, 64)))
+    w.scene.opacity_logit[...] -= 3.0
+    w.scene.log_scale[...] += 0.7
+    r = renderer_for(w, tile=tile, ppt=ppt, wave_w=sw, batch=batch, schedule=schedule, cap=1 << 20)
+    P = DeviceParams.from_scene(w.scene)
+    G = _up(w, 3)
+    r.forward(P)
+    ranges = seg_np(r, "ranges", np.uint32).reshape(-1, 2).astype(np.int64)
+    assert (ranges[:, 1] - ranges[:, 0]).max() > 2 * 256 + 1
+    grads = DeviceParams.zeros_like(P)
+    r.backward(P, torch.from_numpy(G).cuda(), 0, grads)
+    torch.cuda.synchronize()
+    assert grad_report(flat_grads(grads), oracle.backward(w.scene, w.cams, G, mode=0))["fail"] == 0
+
+
 def test_backward_matches_oracle_gradient(oracle):
     w = small(seed=105, n=1500, sizes=((80, 60), (48, 64)))
     r = renderer_for(w)
