@@ -153,13 +153,16 @@ __global__ void k_cell_keys(const uint32_t* cell_of, int64_t n, int64_t n_active
 // rows as it holds, in two launches per batch: k_gather_rows writes
 // scratch[r][k] = row[r][from[k]], k_copy_back_rows returns the rows.  Bound
 // by launches when done row by row (358 launches of about 3 us for a 500k
-// model with moments, 1.23 ms a regrouping); in batches (0.42 ms) it is bound
-// by its four accesses per element.  A thread takes four consecutive positions of kGatherRows
-// rows: the permutation is read once for them, their 16 loads (scattered, but
-// near each other where the model was already grouped) are in flight
-// together, and the scratch rows (stride a multiple of four words) are
-// written 16 bytes at a time.
-constexpr int kGatherRows = 4;
+// model with moments, 1.19 ms a regrouping of which 5% of the Gaussians move);
+// in batches (0.42 ms) it is bound by its four accesses per element.  A thread
+// takes four consecutive positions of kGatherRows rows: the permutation is read
+// once for them, their eight loads (scattered, but near each other where the
+// model was already grouped) are in flight together, and the scratch rows
+// (stride a multiple of four words) are written 16 bytes at a time.  More rows
+// at once compete for the caches where the model is in no order (3M
+// Gaussians: 7.5, 8.8, 9.4 and 9.4 ms with one, two, four and eight, 9.2 row by
+// row; grouped already: 1.71, 1.58, 1.56 and 1.60, 3.1 row by row).
+constexpr int kGatherRows = 2;
 
 __global__ __launch_bounds__(256) void k_gather_rows(RowBatch b, const uint32_t* from, int64_t len, int64_t stride,
                                                      uint32_t* scratch) {
