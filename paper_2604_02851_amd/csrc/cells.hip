@@ -155,20 +155,24 @@ __global__ void k_cell_keys(const uint32_t* cell_of, int64_t n, int64_t n_active
 // by launches when done row by row (358 launches of about 3 us for a 500k
 // model with moments, 1.19 ms a regrouping of which 5% of the Gaussians move);
 // in batches (0.42 ms) it is bound by its four accesses per element.  A thread
-// takes four consecutive positions of kGatherRows rows: the permutation is read
-// once for them, their eight loads (scattered, but near each other where the
-// model was already grouped) are in flight together, and the scratch rows
-// (stride a multiple of four words) are written 16 bytes at a time.  More rows
-// at once compete for the caches where the model is in no order (3M
-// Gaussians: 7.5, 8.8, 9.4 and 9.4 ms with one, two, four and eight, 9.2 row by
-// row; grouped already: 1.71, 1.58, 1.56 and 1.60, 3.1 row by row).
-constexpr int kGatherRows = 2;
+// takes four consecutive positions of R rows: the permutation is read once for
+// them, their loads (scattered, but near each other where the model was already
+// grouped) are in flight together, and the scratch rows (stride a multiple of
+// four words) are written 16 bytes at a time.  One row gives launches of up to
+// kOneRowWords words more workgroups (100k Gaussians of which 5% move 163 us,
+// 195 with two or four rows; 500k 420, 427, 420); past them two rows read the
+// permutation half as often and still leave the caches to few rows where the
+// model is in no order (3M Gaussians in no order 7.4, 8.7 and 9.3 ms with one,
+// two and four, 9.2 row by row; grouped already 1.70, 1.58 and 1.56, 3.1 row by
+// row).
+constexpr int64_t kOneRowWords = 8ll << 20;
 
+template <int R>
 __global__ __launch_bounds__(256) void k_gather_rows(RowBatch b, const uint32_t* from, int64_t len, int64_t stride,
                                                      uint32_t* scratch) {
   const int64_t k = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (k >= len) return;
-  const int r0 = (int)blockIdx.y * kGatherRows;
+  const int r0 = (int)blockIdx.y * R;
   uint32_t src[4];
   if (k + 4 <= len) {
     const uint4 f = *reinterpret_cast<const uint4*>(from + k);
@@ -177,15 +181,15 @@ __global__ __launch_bounds__(256) void k_gather_rows(RowBatch b, const uint32_t*
 #pragma unroll
     for (int c = 0; c < 4; ++c) src[c] = from[k + c < len ? k + c : len - 1];   // (repeats land in the padding)
   }
-  uint4 v[kGatherRows];
+  uint4 v[R];
 #pragma unroll
-  for (int q = 0; q < kGatherRows; ++q) {
+  for (int q = 0; q < R; ++q) {
     if (r0 + q >= b.count) continue;   // uniform
     const uint32_t* row = b.row[r0 + q];
     v[q] = make_uint4(row[src[0]], row[src[1]], row[src[2]], row[src[3]]);
   }
 #pragma unroll
-  for (int q = 0; q < kGatherRows; ++q)
+  for (int q = 0; q < R; ++q)
     if (r0 + q < b.count) *reinterpret_cast<uint4*>(scratch + (int64_t)(r0 + q) * stride + k) = v[q];
 }
 
@@ -233,8 +237,10 @@ hipError_t launch_sort_cells(const Plan& pl, const gs_params& p, const gs_params
   RowBatcher rows(scratch_words, [&](const RowBatch& batch, int64_t len) {
     const int64_t stride = row_stride(len);
     const unsigned g = (unsigned)((len + 1023) / 1024);
-    hipLaunchKernelGGL(k_gather_rows, dim3(g, (unsigned)((batch.count + kGatherRows - 1) / kGatherRows)), dim3(256), 0,
-                       st, batch, from, len, stride, scratch);
+    const bool one = batch.count * len <= kOneRowWords;
+    hipLaunchKernelGGL(one ? k_gather_rows<1> : k_gather_rows<2>,
+                       dim3(g, (unsigned)(one ? batch.count : (batch.count + 1) / 2)), dim3(256), 0, st, batch, from,
+                       len, stride, scratch);
     hipLaunchKernelGGL(k_copy_back_rows, dim3(g, (unsigned)batch.count), dim3(256), 0, st, batch, len, stride, scratch);
   });
   const int nk = (p.sh_degree + 1) * (p.sh_degree + 1);

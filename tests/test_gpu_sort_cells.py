@@ -167,3 +167,24 @@ def test_whole_batches_of_rows(oracle):
     for a, e in zip(_rows(m, na) + _rows(v, na), active):
         assert np.array_equal(a, e[:, order[:na]])
     assert np.array_equal(ids.cpu().numpy(), order.astype(np.int32))
+
+
+@pytest.mark.parametrize("n,views,degree", [(699_050, 1, 3), (699_052, 1, 3), (131_071, 8, 1), (600_011, 8, 0)])
+def test_rows_at_once_either_side_of_the_rule(n, views, degree):
+    """Batches gathered one row and two rows at a time (an odd row left over),
+    on a permutation known from a stable sort."""
+    w = S.small_workload(143, 16, 1.0, degree, [(32, 32)] * views, dist=3.0)
+    r = Renderer(w.cams, n, degree, key_capacity=1 << 16)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    nk = (degree + 1) ** 2
+    P = DeviceParams(*[torch.randn(*s, device="cuda", generator=gen) for s in ((3, n), (3, n), (4, n), (n,), (3 * nk, n))],
+                     degree)
+    before = [t.clone() for t in P.tensors()]
+    cells = torch.randint(0, 500, (n,), dtype=torch.int32, device="cuda", generator=gen)
+    order = torch.sort(cells, stable=True)[1]
+    want = cells[order].clone()
+    r.ctx.sort_cells(P, cells, 500, r.ws)
+    torch.cuda.synchronize()
+    assert torch.equal(cells, want)
+    for a, b in zip(P.tensors(), before):
+        assert torch.equal(a, b[..., order])
