@@ -32,8 +32,9 @@
 // stay in scalar lane masks (a pixel that stopped is a cleared bit, not a sign
 // of T to test), the clamp runs only where an opacity can reach it, and a
 // splat's own factors are applied once to its totals at the flush.  1M
-// Gaussians, 16 views: forward 1.13 -> 0.92 ms (1.05e9 -> 0.70e9 vector
-// instructions), adjoint 1.92 -> 1.69 ms (1.53e9 -> 1.07e9); both at eight
+// Gaussians, 16 mixed views, 32x32 tiles in batches of 64 at four pixels per lane
+// and sub-tiles 16 wide: forward 1.27 -> 0.98 ms (0.99e9 -> 0.71e9 vector
+// instructions), adjoint 2.14 -> 1.87 ms (1.53e9 -> 1.23e9); both at eight
 // wavefronts per SIMD instead of seven.
 #include "internal.h"
 
@@ -896,7 +897,12 @@ __global__ __launch_bounds__(TW* TH / PPT) void k_composite_bwd(BwdArgs a) {
   composite_bwd_tile<TW, TH, PPT, SW, BATCH>(a, tile_of_block(blockIdx.x, (uint32_t)a.ntiles, a.schedule), sm);
 }
 
-// Persistent (schedules 2 and 3), as k_composite_persistent.
+// Persistent (schedules 2 and 3), as k_composite_persistent.  Held to seven
+// wavefronts per SIMD, for the shapes with four pixels per lane: at eight they
+// take up to 7% longer (100k Gaussians in two views of 1280x720, 32x32 tiles,
+// batches of 64: 265 us at seven, 279 at eight); 32x32 tiles with one pixel per
+// lane would gain a quarter (1M Gaussians in four views 2052 and 1557), with
+// two 5%.
 template <int TW, int TH, int PPT, int SW, int BATCH>
 __global__ __launch_bounds__(TW* TH / PPT) __attribute__((amdgpu_waves_per_eu(7))) void k_composite_bwd_persistent(
     BwdArgs a) {

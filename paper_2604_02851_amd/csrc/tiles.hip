@@ -267,15 +267,9 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t value, int64_t count) {
 // histogram (copy lane % kHistCopies; the copies of a digit are adjacent
 // words, so in different banks).  A skewed digit (the exponent byte of depth
 // keys) then meets at most 64 / kHistCopies lanes of one wavefront at each
-// address instead of 64.  Counts are stored digit-major, hist[d * nblocks +
-// chunk].
+// address instead of 64.  Counts are stored where hist_at says.
 constexpr int kHistCopies = 1024 / B;
 
-// Sorts of up to kDirectChunks chunks scan no histogram: it is stored chunk by
-// chunk instead of digit by digit, and each scatter workgroup adds up the rows
-// of the chunks before its own itself (coalesced, from L2).  The scan costs two
-// launches of 4 to 5 us a pass however few chunks there are; the rows cost a
-// workgroup about 1 us per 32 chunks.
 // Chunk of workgroup blockIdx.x of a scatter over `chunks` chunks (chunks or more:
 // none).  Workgroups are dealt to the eight XCDs in turn; each takes a
 // contiguous run of chunks, as the lines where a digit's run of one chunk ends
@@ -290,8 +284,16 @@ __device__ __forceinline__ uint32_t xcd_chunk(uint32_t chunks) {
 }
 inline unsigned xcd_grid(int64_t chunks) { return (unsigned)((chunks + 7) / 8 * 8); }
 
+// Sorts of up to kDirectChunks chunks scan no histogram: it is stored chunk by
+// chunk instead of digit by digit, and each scatter workgroup adds up the rows
+// of the chunks before its own itself (coalesced, from L2).  The scan costs two
+// launches of 4 to 5 us a pass however few chunks there are; the rows cost a
+// workgroup about 1 us per 32 chunks.
 constexpr int64_t kDirectChunks = 320;
 
+// Where a histogram holds the count of a digit in a chunk: digit by digit
+// (digit * nblocks + chunk), as the scan wants it, or chunk by chunk (chunk *
+// 256 + digit) where it is read as it is.
 __device__ __forceinline__ int64_t hist_at(uint32_t digit, uint32_t chunk, int64_t nblocks, bool direct) {
   return direct ? (int64_t)chunk * 256 + digit : (int64_t)digit * nblocks + chunk;
 }
@@ -1155,8 +1157,8 @@ __global__ __launch_bounds__(256) void k_order_scatter(const uint2* ranges, uint
 }
 
 // ---- tile lists of small models ----------------------------------------------
-// The sort's launches take 4 to 15 us each however little they hold: 17 of
-// them, 110 us, for a thousand Gaussians.  Where every pair can be compared
+// The sort's launches take 4 to 15 us each however little they hold: 56 us for a
+// thousand Gaussians in one small view.  Where every pair can be compared
 // with every other of its view and every tile with every pair, three launches
 // build the same lists: k_small_rank gives each visible pair its place in its
 // view's depth order by counting the pairs before it, k_small_count counts for
