@@ -259,6 +259,7 @@ struct ProjArgs {
   uint2* rect;               // (x0 | y0 << 16, x1 | y1 << 16)
   float4* rec;
   bool stream_rec;           // the call's records exceed the last-level cache
+  int whole_lanes;
   uint64_t* vmask;           // per Gaussian: the views of this call that see it
   const uint32_t* cell_of;   // preculling (null = off)
   const uint8_t* cell_mask;
@@ -268,14 +269,18 @@ struct ProjArgs {
 // Visible lanes from which a wavefront stores the entries of all of its lanes
 // (a wavefront's 256 bytes of a 4-byte array are two lines or more).  With few
 // visible lanes the other lanes' entries cost more than the partly written
-// lines, the more so where the records go past the caches; each line lies where
-// no part of visible Gaussians is slower than with their entries alone.  1M
-// Gaussians in random order, SH degree 0.  Eight views, past the caches (us at
-// 12, 20, 24, 28 and 64 lanes): 15% visible 101, 87, 86, 86, 90; 20% 109, 87,
-// 86, 86, 89; 25% 107, 91, 113, 118, 120; 30% 106, 110, 121, 157, 164; 50% 105,
-// 103, 104, 109, 233; all 106.  Four views, in the caches (at 4, 12, 24 and 64):
-// 5% 50, 47, 48, 47; 15% 59, 55, 55, 55; 25% 59, 60, 65, 66; 50% 60, 60, 60, 82.
-constexpr int kWholeLanes = 12, kWholeLanesStreamed = 20;
+// lines, as long as the lines that those touch still meet in the last-level
+// cache: kSparseLanes where all records are 1.25 to 1.75 times that cache,
+// kWholeLanes where they fit it or are too many for any of this.  Gaussians in
+// random order, SH degree 0, us with only their own entries / from 12 / from 20
+// lanes.  1M, six views (288 MB of records): 15% visible 79 / 80 / 79, 30% 84 /
+// 85 / 92.  Eight views (384 MB): 15% 90 / 102 / 89, 20% 90 / 106 / 88, 25% 120 /
+// 107 / 97, 30% 163 / 105 / 112, 40% 214 / 107 / 109.  Ten views (480 MB): 15% 102
+// / 111 / 101, 20% 169 / 125 / 162, 25% 215 / 124 / 172.  2M, eight views (768
+// MB): 10% 202 / 194 / 201, 15% 279 / 240 / 277, 25% 357 / 210 / 327.  1M, four
+// views (192 MB, from 4 / 12 / 24 lanes): 5% 50 / 47 / 48, 25% 59 / 60 / 65, 50%
+// 60 / 60 / 60 (82 with their own).
+constexpr int kWholeLanes = 12, kSparseLanes = 20;
 
 constexpr int kViewWaves = 1;   // (the per-Gaussian view mask assumes a single wavefront per Gaussian)
 static_assert(kViewWaves == 1, "one wavefront writes a Gaussian's view mask");
@@ -399,7 +404,7 @@ void k_project(ProjArgs a) {
     // records through LDS so that each store covers whole lines, past the
     // caches when all of them exceed the last one: 252 us.
     const uint64_t seen = __ballot(cnt != 0u);
-    const bool whole = full && __popcll(seen) >= (a.stream_rec ? kWholeLanesStreamed : kWholeLanes);   // uniform
+    const bool whole = full && __popcll(seen) >= a.whole_lanes;   // uniform
     if (whole || cnt != 0u) {
       (a.rect + o)[lane] = rect;
       (a.depth + o)[lane] = depth;
@@ -702,7 +707,9 @@ hipError_t launch_project(const Plan& pl, const ParamPtrs& p, const gs_camera* c
   a.count = seg<uint32_t>(ws, pl.ws.count);
   a.rect = seg<uint2>(ws, pl.ws.rect);
   a.rec = seg<float4>(ws, pl.ws.rec);
-  a.stream_rec = (int64_t)nv * p.n * (int64_t)(sizeof(float) * kRecFloats) > kLastCacheBytes;
+  const int64_t rec_bytes = (int64_t)nv * p.n * (int64_t)(sizeof(float) * kRecFloats);
+  a.stream_rec = rec_bytes > kLastCacheBytes;
+  a.whole_lanes = 4 * rec_bytes > 5 * kLastCacheBytes && 4 * rec_bytes <= 7 * kLastCacheBytes ? kSparseLanes : kWholeLanes;
   a.vmask = seg<uint64_t>(ws, pl.ws.vmask);
   a.cell_of = pl.cell_of;
   a.cell_mask = pl.cell_mask;

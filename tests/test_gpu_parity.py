@@ -236,11 +236,12 @@ def test_records_around_the_whole_line_rule(n, keep, deg):
     assert np.array_equal(seg_np(r2, "depth", np.uint32).reshape(2, n)[left], depth[left])
 
 
-@pytest.mark.parametrize("keep", [1, 11, 12, 23, 24, 25, 64])
-def test_streamed_records_around_the_whole_line_rule(keep):
+@pytest.mark.parametrize("views,keep", [(23, 1), (23, 11), (23, 12), (30, 12), (30, 19), (30, 20), (30, 64), (40, 12)])
+def test_streamed_records_around_the_whole_line_rule(views, keep):
     """The same where all records exceed the last-level cache and are stored
-    past it (23 views of 250,000 Gaussians, 276 MB)."""
-    n, views = 250_007, 23
+    past it (250,000 Gaussians: 23 views 276 MB and 40 views 480 MB, from 12 lanes;
+    30 views 360 MB, from 20)."""
+    n = 250_007
     w = small(seed=165, n=n, sizes=((64, 48),) * views, deg=0)
     sc = w.scene
     r = renderer_for(w, cap=1 << 16)
