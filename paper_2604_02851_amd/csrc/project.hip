@@ -402,7 +402,7 @@ void k_project(ProjArgs a) {
     // 446 us at 1M Gaussians and 16 views.  A wavefront with several visible
     // lanes stores every lane's (the others' are never read), the 48-byte
     // records through LDS so that each store covers whole lines, past the
-    // caches when all of them exceed the last one: 252 us.
+    // caches when all of them exceed the last one: 246 us.
     const uint64_t seen = __ballot(cnt != 0u);
     const bool whole = full && __popcll(seen) >= a.whole_lanes;   // uniform
     if (whole || cnt != 0u) {
